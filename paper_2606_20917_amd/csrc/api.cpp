@@ -114,6 +114,12 @@ static int resolve_variant(int shape, int P, int dtype) {
   return dtype == NIR_F64 ? def64[P] : def32[P];
 }
 
+// whether launch_helm_auto takes gathered coefficients (OpArgs::map) for this basis now: the hex
+// pencil kernels do, the generic one does not
+bool helm_gathers(const nir_basis* basis, int dtype) {
+  return basis->shape == kHex && resolve_variant(kHex, basis->P, dtype) != NIR_VARIANT_GENERIC;
+}
+
 // the fused Helmholtz apply with the selected kernel variant (native contractions)
 nir_status launch_helm_auto(const nir_basis* basis, int dtype, int deformed, const OpArgs& a, hipStream_t s) {
   int v = resolve_variant(basis->shape, basis->P, dtype);

@@ -36,10 +36,12 @@ __global__ void __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(hex_waves_target<P, T, E, TP, (GP && DEF) ? 4 : 3>())))
 k_helm_hex(const T* __restrict__ tabs, const T* __restrict__ x,
                                                   T* __restrict__ y, const T* __restrict__ helm,
-                                                  const T* __restrict__ wq, T lambda, int64_t nelmt) {
+                                                  const T* __restrict__ wq, T lambda, int64_t nelmt,
+                                                  const int32_t* __restrict__ map) {
   // one element group per block (no grid-stride loop: the basis operands stay short-lived)
   __shared__ T lds[HexPencilDims<P, T, E, TP>::LDS];
-  helm_hex_group<P, T, DEF, IU, E, PF, TP, GP>(tabs, x, y, helm, wq, lambda, nelmt, int64_t(blockIdx.x) * E, lds);
+  helm_hex_group<P, T, DEF, IU, E, PF, TP, GP>(tabs, x, y, helm, wq, lambda, nelmt, int64_t(blockIdx.x) * E, lds,
+                                                   map);
 }
 
 // variant: 0 = E_max elements per 256-thread block, 1 = same with the point loop unrolled twice,
@@ -48,33 +50,33 @@ k_helm_hex(const T* __restrict__ tabs, const T* __restrict__ x,
 // ahead, 6 = 4 with the same (both are 0 and 4 for affine elements, which stream no factors)
 template <int P, class T, bool DEF, int IU, int E, bool PF, bool TP = false, bool GP = false>
 static void launch_cfg(const T* tb, const T* x, T* y, const T* helm, const T* wq, T lam, int64_t nelmt,
-                       hipStream_t s) {
+                       const int32_t* map, hipStream_t s) {
   using D = HexPencilDims<P, T, E, TP>;
   const int64_t nb = (nelmt + E - 1) / E;
   hipLaunchKernelGGL((k_helm_hex<P, T, DEF, IU, E, PF, TP, GP>), dim3(static_cast<unsigned>(nb)), dim3(D::BLOCK), 0, s,
-                     tb, x, y, helm, wq, lam, nelmt);
+                     tb, x, y, helm, wq, lam, nelmt, map);
 }
 
 template <int P, class T, bool DEF>
 static void launch_var(int variant, const T* tb, const T* x, T* y, const T* helm, const T* wq, T lam,
-                       int64_t nelmt, hipStream_t s) {
+                       int64_t nelmt, const int32_t* map, hipStream_t s) {
   constexpr int EMAX = 256 / ((P + 1) * (P + 1));
   switch (variant) {
-    case 1: launch_cfg<P, T, DEF, 2, EMAX, false>(tb, x, y, helm, wq, lam, nelmt, s); break;
-    case 2: launch_cfg<P, T, DEF, 1, 1, false>(tb, x, y, helm, wq, lam, nelmt, s); break;
-    case 3: launch_cfg<P, T, DEF, 1, hex_block_elems<P, T>(kFamPF), true>(tb, x, y, helm, wq, lam, nelmt, s); break;
-    case 4: launch_cfg<P, T, DEF, 1, EMAX, false, true>(tb, x, y, helm, wq, lam, nelmt, s); break;
+    case 1: launch_cfg<P, T, DEF, 2, EMAX, false>(tb, x, y, helm, wq, lam, nelmt, map, s); break;
+    case 2: launch_cfg<P, T, DEF, 1, 1, false>(tb, x, y, helm, wq, lam, nelmt, map, s); break;
+    case 3: launch_cfg<P, T, DEF, 1, hex_block_elems<P, T>(kFamPF), true>(tb, x, y, helm, wq, lam, nelmt, map, s); break;
+    case 4: launch_cfg<P, T, DEF, 1, EMAX, false, true>(tb, x, y, helm, wq, lam, nelmt, map, s); break;
     case 5:
       if constexpr (DEF)
-        launch_cfg<P, T, DEF, 1, hex_block_elems<P, T>(kFamGP), false, false, true>(tb, x, y, helm, wq, lam, nelmt, s);
-      else launch_cfg<P, T, DEF, 1, EMAX, false>(tb, x, y, helm, wq, lam, nelmt, s);
+        launch_cfg<P, T, DEF, 1, hex_block_elems<P, T>(kFamGP), false, false, true>(tb, x, y, helm, wq, lam, nelmt, map, s);
+      else launch_cfg<P, T, DEF, 1, EMAX, false>(tb, x, y, helm, wq, lam, nelmt, map, s);
       break;
     case 6:
       if constexpr (DEF)
-        launch_cfg<P, T, DEF, 1, hex_block_elems<P, T>(kFamSGP), false, true, true>(tb, x, y, helm, wq, lam, nelmt, s);
-      else launch_cfg<P, T, DEF, 1, EMAX, false, true>(tb, x, y, helm, wq, lam, nelmt, s);
+        launch_cfg<P, T, DEF, 1, hex_block_elems<P, T>(kFamSGP), false, true, true>(tb, x, y, helm, wq, lam, nelmt, map, s);
+      else launch_cfg<P, T, DEF, 1, EMAX, false, true>(tb, x, y, helm, wq, lam, nelmt, map, s);
       break;
-    default: launch_cfg<P, T, DEF, 1, EMAX, false>(tb, x, y, helm, wq, lam, nelmt, s); break;
+    default: launch_cfg<P, T, DEF, 1, EMAX, false>(tb, x, y, helm, wq, lam, nelmt, map, s); break;
   }
 }
 
@@ -88,9 +90,9 @@ static nir_status launch_P(const nir_basis* b, int deformed, int variant, const 
   const T* helm = static_cast<const T*>(a.helm);
   const T lam = T(a.lambda);
   if (deformed)
-    launch_var<P, T, true>(variant, tb, x, y, helm, wq, lam, a.nelmt, s);
+    launch_var<P, T, true>(variant, tb, x, y, helm, wq, lam, a.nelmt, a.map, s);
   else
-    launch_var<P, T, false>(variant, tb, x, y, helm, wq, lam, a.nelmt, s);
+    launch_var<P, T, false>(variant, tb, x, y, helm, wq, lam, a.nelmt, a.map, s);
   return hip_check(hipGetLastError(), "hex Helmholtz launch");
 }
 

@@ -17,21 +17,21 @@ constexpr bool eo_staged_factors() {
 template <int P, class T, bool DEF, int E, bool TP, bool SF = eo_staged_factors<P, T, DEF>() && !TP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(hex_waves_target<P, T, E, TP>())))
 k_helm_hex_eo(const T* __restrict__ tabs, const T* __restrict__ x, T* __restrict__ y, const T* __restrict__ helm,
-              const T* __restrict__ wq, T lambda, int64_t nelmt) {
+              const T* __restrict__ wq, T lambda, int64_t nelmt, const int32_t* __restrict__ map) {
   using D = HexPencilDims<P, T, E, TP>;
   __shared__ T lds[D::LDS + (SF ? E * 7 * D::NQ + D::BLOCK : 0)];
   helm_hex_eo_group<P, T, DEF, E, TP, true, 1, false, SF>(tabs, x, y, helm, wq, lambda, nelmt,
-                                                           int64_t(blockIdx.x) * E, lds);
+                                                           int64_t(blockIdx.x) * E, lds, nullptr, nullptr, nullptr, map);
 }
 
 template <int P, class T, bool DEF, bool TP>
 static void launch_eo_cfg(const T* tb, const T* x, T* y, const T* helm, const T* wq, T lam, int64_t nelmt,
-                          hipStream_t s) {
+                          const int32_t* map, hipStream_t s) {
   constexpr int E = DEF ? hex_block_elems<P, T>(TP ? kFamEOS : kFamEO) : 256 / ((P + 1) * (P + 1));
   using D = HexPencilDims<P, T, E, TP>;
   const int64_t nb = (nelmt + E - 1) / E;
   hipLaunchKernelGGL((k_helm_hex_eo<P, T, DEF, E, TP>), dim3(static_cast<unsigned>(nb)), dim3(D::BLOCK), 0, s, tb,
-                     x, y, helm, wq, lam, nelmt);
+                     x, y, helm, wq, lam, nelmt, map);
 }
 
 template <int P, class T>
@@ -46,14 +46,14 @@ static nir_status launch_eo_P(const nir_basis* b, int deformed, bool split, cons
   const T lam = T(a.lambda);
   if (deformed) {
     if (split)
-      launch_eo_cfg<P, T, true, true>(tb, x, y, helm, wq, lam, a.nelmt, s);
+      launch_eo_cfg<P, T, true, true>(tb, x, y, helm, wq, lam, a.nelmt, a.map, s);
     else
-      launch_eo_cfg<P, T, true, false>(tb, x, y, helm, wq, lam, a.nelmt, s);
+      launch_eo_cfg<P, T, true, false>(tb, x, y, helm, wq, lam, a.nelmt, a.map, s);
   } else {
     if (split)
-      launch_eo_cfg<P, T, false, true>(tb, x, y, helm, wq, lam, a.nelmt, s);
+      launch_eo_cfg<P, T, false, true>(tb, x, y, helm, wq, lam, a.nelmt, a.map, s);
     else
-      launch_eo_cfg<P, T, false, false>(tb, x, y, helm, wq, lam, a.nelmt, s);
+      launch_eo_cfg<P, T, false, false>(tb, x, y, helm, wq, lam, a.nelmt, a.map, s);
   }
   return hip_check(hipGetLastError(), "hex even-odd Helmholtz launch");
 }

@@ -166,7 +166,8 @@ __device__ __forceinline__ void tri_factors(const double* J1, const double* A2, 
 // flight in registers through sweeps A and B; they are then stored into LDS after `lds`'s
 // HexPencilDims<P,T,E,TP>::LDS values, where the point loop reads them.  Every block's whole
 // factor stream is then in flight at once, as in a plain copy.  The caller's LDS holds
-// HexPencilDims<P,T,E,TP>::LDS + E 7 Q^3 + BLOCK values (the last BLOCK a junk row).
+// HexPencilDims<P,T,E,TP>::LDS + E 7 Q^3 + BLOCK values (the last BLOCK a junk row).  map as in
+// helm_hex_group.
 template <int P, class T, bool DEF, int E_ = 256 / ((P + 1) * (P + 1)), bool TP = false, bool GP = false,
           int NF = 1, bool TRI = false, bool SF = false>
 __device__ __forceinline__ void helm_hex_eo_group(const T* __restrict__ tabs, const T* __restrict__ x,
@@ -174,7 +175,8 @@ __device__ __forceinline__ void helm_hex_eo_group(const T* __restrict__ tabs, co
                                                   const T* __restrict__ wq, T lambda, int64_t nelmt, int64_t base,
                                                   T* __restrict__ lds, const double* __restrict__ vtx = nullptr,
                                                   const double* __restrict__ z1 = nullptr,
-                                                  const double* __restrict__ w1 = nullptr) {
+                                                  const double* __restrict__ w1 = nullptr,
+                                                  const int32_t* __restrict__ map = nullptr) {
   using D = HexPencilDims<P, T, E_, TP>;
   using F = EoDims<P>;
   constexpr int BLOCK = D::BLOCK;
@@ -201,13 +203,23 @@ __device__ __forceinline__ void helm_hex_eo_group(const T* __restrict__ tabs, co
     // the coefficients, then the block's factors, with buffer loads and no branch (reads past a
     // descriptor's size return zeros), so that each wait counts exactly the requests it needs:
     // the coefficients are requested first because the vector memory counter completes in order
-    const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<T*>(x + base * M), short(0), (ne > 0 ? ne : 0) * M * int(sizeof(T)), 0x00020000);
     const __amdgpu_buffer_rsrc_t frs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<T*>(helm + base * NF7), short(0), (ne > 0 ? ne : 0) * NF7 * int(sizeof(T)), 0x00020000);
     T xv[PERX];
+    if (map) {   // through the map; threads past the end read entry 0
+      const __amdgpu_buffer_rsrc_t mrs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<int32_t*>(map + base * M), short(0), (ne > 0 ? ne : 0) * M * 4, 0x00020000);
+      int32_t gi[PERX];
 #pragma unroll
-    for (int k = 0; k < PERX; ++k) xv[k] = buf_load<T>(xrs, t * int(sizeof(T)), k * BLOCK * int(sizeof(T)));
+      for (int k = 0; k < PERX; ++k) gi[k] = buf_load<int32_t>(mrs, t * 4, k * BLOCK * 4);
+#pragma unroll
+      for (int k = 0; k < PERX; ++k) xv[k] = x[gi[k]];
+    } else {
+      const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<T*>(x + base * M), short(0), (ne > 0 ? ne : 0) * M * int(sizeof(T)), 0x00020000);
+#pragma unroll
+      for (int k = 0; k < PERX; ++k) xv[k] = buf_load<T>(xrs, t * int(sizeof(T)), k * BLOCK * int(sizeof(T)));
+    }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int k = 0; k < PERF; ++k) fv[k] = buf_load<T>(frs, t * int(sizeof(T)), k * BLOCK * int(sizeof(T)));
@@ -221,10 +233,14 @@ __device__ __forceinline__ void helm_hex_eo_group(const T* __restrict__ tabs, co
     }
   } else {
     // ---- stage coefficients (coalesced) into padded mode pencils
-    for (int f = t; f < ne * M; f += BLOCK) {
+    auto put = [&](int f, T v) {
       const int e2 = f / M, m = f - e2 * M, pq = m / P, r = m - pq * P;
-      lds[e2 * SLAB + pq * PP + r] = x[base * M + f];
-    }
+      lds[e2 * SLAB + pq * PP + r] = v;
+    };
+    if (map)
+      gather_coefs<E * M, BLOCK>(x, map + base * M, ne * M, t, put);
+    else
+      for (int f = t; f < ne * M; f += BLOCK) put(f, x[base * M + f]);
   }
   __syncthreads();
 

@@ -180,6 +180,7 @@ struct OpArgs {
   const void* helm;
   double lambda;
   int64_t nelmt;
+  const int32_t* map;   // hex pencil kernels: coefficient f of the batch is in0[map[f]] (null: in0[f])
 };
 
 enum OpKind { kOpBwd = 0, kOpIProd = 1, kOpPhysDeriv = 2, kOpIProdDeriv = 3, kOpHelm = 4 };
@@ -238,6 +239,7 @@ nir_status launch_helm_dense(const nir_basis* b, int dtype, const OpArgs& a, hip
 nir_status launch_helm_dense_f16split(const nir_basis* b, const OpArgs& a, hipStream_t s);
 nir_status build_dense_refs(nir_basis* b);
 // the fused Helmholtz apply with the currently selected kernel variant (native contractions)
+bool helm_gathers(const nir_basis* basis, int dtype);
 nir_status launch_helm_auto(const nir_basis* basis, int dtype, int deformed, const OpArgs& a, hipStream_t s);
 nir_status launch_points(const nir_basis* b, int64_t nelmt, const double* verts, double amp, double* xyz,
                          hipStream_t s);

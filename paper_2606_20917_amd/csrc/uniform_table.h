@@ -44,6 +44,27 @@ __device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, int voff, int so
     return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
 }
 
+// The group's coefficients 0 .. n-1 through a local-to-global map: first[f] = x[map[f]], handed to
+// `put(f, value)`.  The map entries of a thread are requested at once, then the values, so that a
+// block waits for two memory latencies and not for two per round of its threads (NMAX: the most
+// coefficients of a group); threads past the end read entry n - 1 and put nothing.  Against a
+// gather pass of its own the assembled FP32 apply of 32^3 hexahedra at P = 6 takes 81 us, not 100.
+template <int NMAX, int BLOCK, class T, class F>
+__device__ __forceinline__ void gather_coefs(const T* __restrict__ x, const int32_t* __restrict__ map, int n, int t,
+                                             F&& put) {
+  constexpr int PER = (NMAX + BLOCK - 1) / BLOCK;
+  if (n <= 0) return;
+  int32_t gi[PER];
+  T v[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) gi[k] = map[min(t + k * BLOCK, n - 1)];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) v[k] = x[gi[k]];
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (t + k * BLOCK < n) put(t + k * BLOCK, v[k]);
+}
+
 template <int P, class T>
 struct HexTabC {
   const_ptr<T> t;
