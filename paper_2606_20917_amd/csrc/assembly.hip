@@ -8,6 +8,7 @@
 // reductions use a fixed block count and a fixed summation order, so results
 // are bitwise reproducible.  No atomics are used on any FP path.
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -20,6 +21,7 @@ namespace nir {
 
 constexpr int kRedBlocks = 1024;   // partial sums per reduction (fixed: deterministic order)
 constexpr int kRedThreads = 256;
+constexpr int kScatterEntries = 4;   // entries of a scatter-reduce row read together
 
 // ---------------------------------------------------------------- C0 map
 __host__ __device__ inline int64_t c0_g1(int64_t i, int p, int P) {
@@ -44,15 +46,43 @@ __global__ void k_gather(const int32_t* __restrict__ l2g, const T* __restrict__ 
     xl[t] = xg[l2g[t]];
 }
 
+// Sum of CSR row g over its entries in ascending (element, mode) order.  A row is a chain of
+// dependent reads (offsets, index, value) and holds one to eight entries on a mesh of hexahedra, so
+// K entries go through every stage together: three memory latencies for a row of up to K.
+template <class T>
+__device__ __forceinline__ T row_sum(const int32_t* __restrict__ off, const int32_t* __restrict__ idx,
+                                     const T* __restrict__ yl, int64_t g) {
+  constexpr int K = kScatterEntries;
+  const int32_t at = off[g], end = off[g + 1];
+  T s = T(0);
+  for (int32_t k = at; k < end; k += K) {
+    int32_t n[K];
+    T v[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) n[i] = k + i < end ? idx[k + i] : -1;
+#pragma unroll
+    for (int i = 0; i < K; ++i) v[i] = n[i] >= 0 ? yl[n[i]] : T(0);
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+      if (n[i] >= 0) s += v[i];
+  }
+  return s;
+}
+
+// The dispatcher deals blocks to the 8 XCDs in turn; block b takes the work of block xcd_block(b), so
+// that each XCD gets a contiguous run of blocks and its L2 serves the lines that neighbours share.
+__device__ __forceinline__ int xcd_block(int b, int nb) {
+  const int per = nb / 8, x = b % 8;
+  return b < per * 8 ? x * per + b / 8 : b;
+}
+
 // yg[G] = sum over the local entries of G in ascending (element, mode) order
 template <class T>
-__global__ void k_scatter(const int32_t* __restrict__ off, const int32_t* __restrict__ idx, const T* __restrict__ yl,
-                          T* __restrict__ yg, int64_t ng) {
-  for (int64_t g = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; g < ng; g += int64_t(gridDim.x) * blockDim.x) {
-    T s = T(0);
-    for (int32_t k = off[g]; k < off[g + 1]; ++k) s += yl[idx[k]];
-    yg[g] = s;
-  }
+__global__ void __launch_bounds__(256) k_scatter(const int32_t* __restrict__ off, const int32_t* __restrict__ idx,
+                                                 const T* __restrict__ yl, T* __restrict__ yg, int64_t ng) {
+  const int64_t stride = int64_t(gridDim.x) * 256;
+  for (int64_t g = int64_t(xcd_block(blockIdx.x, gridDim.x)) * 256 + threadIdx.x; g < ng; g += stride)
+    yg[g] = row_sum(off, idx, yl, g);
 }
 
 // ---------------------------------------------------------------- Jacobi diagonal
@@ -92,17 +122,41 @@ __global__ void __launch_bounds__(256) k_diag_hex(int P, const T* __restrict__ T
 }
 
 // ---------------------------------------------------------------- BLAS-1 with fixed-order reductions
+// Sum of kRedThreads values in the order of a halving tree (t adds t + 128, t + 64, .., t + 1), by
+// the first wavefront; lane 0 holds it.
+__device__ __forceinline__ double tree_sum(const double* sh) {
+  double s = 0.0;
+  if (threadIdx.x < 64) {
+    const int t = threadIdx.x;
+    s = (sh[t] + sh[t + 128]) + (sh[t + 64] + sh[t + 192]);
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) s += __shfl_down(s, w, 64);
+  }
+  return s;
+}
+
+// Sum over a block of kRedThreads threads in that order; the value reaches every thread.
 __device__ __forceinline__ double block_sum(double v, double* sh) {
   sh[threadIdx.x] = v;
   __syncthreads();
-  for (int w = kRedThreads / 2; w > 0; w >>= 1) {
-    if (int(threadIdx.x) < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-    __syncthreads();
-  }
+  const double s = tree_sum(sh);
+  if (threadIdx.x == 0) sh[0] = s;
+  __syncthreads();
   const double r = sh[0];
   __syncthreads();
   return r;
 }
+
+// Sum of the first `nb` partials of a reduction (the others are zero), every thread of the block:
+// thread t adds partials t, t + 256, .., then the block's tree.  Kernels that need a reduction's
+// result sum its partials themselves, each block the same way, instead of waiting for a launch of
+// one block in between (about 4.6 us of an otherwise idle GPU, three times an iteration).
+__device__ __forceinline__ double sum_partials(const double* __restrict__ part, int nb, double* sh) {
+  double s = 0.0;
+  for (int b = threadIdx.x; b < nb; b += kRedThreads) s += part[b];
+  return block_sum(s, sh);
+}
+static_assert(kRedThreads == 256, "tree_sum adds four values per lane of the first wavefront");
 
 // partial[b] = sum over this block's grid-stride range of a[i]*b[i] (FP64 accumulation)
 template <class TA, class TB>
@@ -116,89 +170,158 @@ __global__ void __launch_bounds__(kRedThreads) k_dot_part(const TA* __restrict__
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-// One block: sums kRedBlocks partials of `nq` quantities (part[q*kRedBlocks + b]) in fixed order
-// into sc[dst + q], then applies a scalar step:
-//   step 0: nothing
-//   step 1: alpha = rz / pAp          (sc: rz=0, pAp=2, alpha=3); breakdown flag if pAp <= 0 or not finite
-//   step 2: beta = rz_new / rz, rz = rz_new  (sc: rz=0, rz_new=1, beta=4)
-__global__ void __launch_bounds__(kRedThreads) k_final(const double* __restrict__ part, int nq, double* __restrict__ sc,
-                                                       int dst, int step, int* __restrict__ flag) {
+// One block: the sum of the first nb partials into sc[dst]
+__global__ void __launch_bounds__(kRedThreads) k_final(const double* __restrict__ part, int nb, double* __restrict__ sc,
+                                                       int dst) {
   __shared__ double sh[kRedThreads];
-  for (int q = 0; q < nq; ++q) {
-    double s = 0.0;
-    for (int b = threadIdx.x; b < kRedBlocks; b += kRedThreads) s += part[q * kRedBlocks + b];
-    s = block_sum(s, sh);
-    if (threadIdx.x == 0) sc[dst + q] = s;
-  }
-  if (threadIdx.x == 0) {
-    if (step == 1) {
-      const double pap = sc[2];
-      if (!(pap > 0.0) || !isfinite(pap)) *flag = 1;
-      sc[3] = (pap > 0.0 && isfinite(pap)) ? sc[0] / pap : 0.0;
-    } else if (step == 2) {
-      const double rz = sc[0], rzn = sc[1];
-      sc[4] = rz != 0.0 ? rzn / rz : 0.0;
-      sc[0] = rzn;
-    }
-  }
+  const double s = sum_partials(part, nb, sh);
+  if (threadIdx.x == 0) sc[dst] = s;
 }
 
-// x += alpha p; r -= alpha Ap; z = r / diag; partial sums of r.z and r.r
-template <class T>
-__global__ void __launch_bounds__(kRedThreads) k_cg_update(T* __restrict__ x, T* __restrict__ r, T* __restrict__ z,
-                                                           const T* __restrict__ p, const T* __restrict__ Ap,
-                                                           const T* __restrict__ dinv, const double* __restrict__ sc,
-                                                           int64_t n, double* __restrict__ part) {
+// One PCG iteration on the vectors of precision T is the element apply and the three kernels below.
+// The reductions' partial sums keep the block and thread order of k_dot_part, whatever kernel
+// forms them, and alpha, beta are formed by every block from the same partials.
+// Bound by memory traffic and, on small meshes, by launches.  32^3 hexahedra, P = 6, FP32: scatter
+// and dot 48.3 -> 36.4 us, update 22.8 -> 16.6 us, direction 10.0 -> 20.0 us (it now updates x as
+// well, so that p is read once for both), three reductions' launches of 14 us gone; 10^3 at P = 4
+// in FP64: eight kernels of 22 us -> three of 10.5 us.
+// Scalars: r.z of the current residual is sc[cur], the next one goes to sc[1 - cur] (two slots, so
+// that no block overwrites what another still reads); sc[2] = p.Ap, sc[3] = alpha, sc[5] = r.r.
+
+// Ap = scatter-reduce of the element results, and the partials of p.Ap on the way.  A partial sums
+// the products of kRedThreads lanes in the order of their rows, so a block of that many threads
+// would walk its rows one after the other, 16 wavefronts on a CU waiting for memory.  SUB groups of
+// kRedThreads threads share the block's rows (row k of a lane goes to group k mod SUB); the values
+// meet in LDS, from where the first group adds the products in row order.
+template <class T, int SUB>
+__global__ void __launch_bounds__(kRedThreads * SUB) k_cg_scatter(const int32_t* __restrict__ off,
+                                                                  const int32_t* __restrict__ idx,
+                                                                  const T* __restrict__ yl, const T* __restrict__ p,
+                                                                  T* __restrict__ Ap, int64_t n,
+                                                                  double* __restrict__ part) {
+  constexpr int ROUNDS = SUB > 1 ? 4 : 1;   // rows of a thread between two exchanges
+  __shared__ T ex[SUB > 1 ? 2 : 1][SUB > 1 ? SUB * ROUNDS : 1][kRedThreads];
   __shared__ double sh[kRedThreads];
-  const T alpha = T(sc[3]);
+  constexpr int64_t stride = int64_t(kRedBlocks) * kRedThreads;
+  const int sub = SUB > 1 ? threadIdx.x / kRedThreads : 0, lane = threadIdx.x - sub * kRedThreads;
+  const int blk = xcd_block(blockIdx.x, gridDim.x);
+  double acc = 0.0;
+  for (int64_t i0 = int64_t(blk) * kRedThreads; i0 < n; i0 += SUB * ROUNDS * stride) {
+#pragma unroll
+    for (int k = 0; k < ROUNDS; ++k) {
+      const int64_t i = i0 + lane + (k * SUB + sub) * stride;
+      const T pv = i < n ? p[i] : T(0);
+      T s = T(0);
+      if (i < n) {
+        s = row_sum(off, idx, yl, i);
+        Ap[i] = s;
+      }
+      if constexpr (SUB > 1) {
+        ex[0][k * SUB + sub][lane] = pv;
+        ex[1][k * SUB + sub][lane] = s;
+      } else {
+        acc += double(pv) * double(s);
+      }
+    }
+    if constexpr (SUB > 1) {
+      __syncthreads();
+      if (sub == 0)
+#pragma unroll
+        for (int k = 0; k < SUB * ROUNDS; ++k) acc += double(ex[0][k][lane]) * double(ex[1][k][lane]);
+      __syncthreads();
+    }
+  }
+  if constexpr (SUB > 1) {
+    if (sub == 0) sh[lane] = acc;
+    __syncthreads();
+    if (sub == 0) acc = tree_sum(sh);
+  } else {
+    acc = block_sum(acc, sh);
+  }
+  if (threadIdx.x == 0) part[blk] = acc;
+}
+
+// alpha = r.z / p.Ap (flag if p.Ap <= 0 or not finite); r -= alpha Ap; partials of r.z and r.r
+// with z = r / diag, which is not stored: the next kernel forms it again from r
+template <class T>
+__global__ void __launch_bounds__(kRedThreads) k_cg_residual(T* __restrict__ r, const T* __restrict__ Ap,
+                                                             const T* __restrict__ dinv, double* __restrict__ sc, int cur,
+                                                             const double* __restrict__ pap_part, int64_t n,
+                                                             double* __restrict__ rz_part, double* __restrict__ rr_part,
+                                                             int* __restrict__ flag) {
+  __shared__ double sh[kRedThreads];
+  const double pap = sum_partials(pap_part, gridDim.x, sh);
+  const bool good = pap > 0.0 && isfinite(pap);
+  const double al = good ? sc[cur] / pap : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (!good) *flag = 1;
+    sc[2] = pap;
+    sc[3] = al;
+  }
+  const T alpha = T(al);
   double srz = 0.0, srr = 0.0;
   for (int64_t i = int64_t(blockIdx.x) * kRedThreads + threadIdx.x; i < n; i += int64_t(kRedBlocks) * kRedThreads) {
-    x[i] += alpha * p[i];
     const T ri = r[i] - alpha * Ap[i];
     r[i] = ri;
     const T zi = ri * dinv[i];
-    z[i] = zi;
     srz += double(ri) * double(zi);
     srr += double(ri) * double(ri);
   }
   srz = block_sum(srz, sh);
   srr = block_sum(srr, sh);
   if (threadIdx.x == 0) {
-    part[blockIdx.x] = srz;
-    part[kRedBlocks + blockIdx.x] = srr;
+    rz_part[blockIdx.x] = srz;
+    rr_part[blockIdx.x] = srr;
   }
 }
 
+// x += alpha p; beta = r.z (new) / r.z; p = r / diag + beta p; `host` (pinned, may be null) gets
+// r.r and the breakdown flag, which the host reads after the stream's next synchronisation
 template <class T>
-__global__ void k_cg_pupdate(T* __restrict__ p, const T* __restrict__ z, const double* __restrict__ sc, int64_t n) {
-  const T beta = T(sc[4]);
-  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x)
-    p[i] = z[i] + beta * p[i];
+__global__ void __launch_bounds__(kRedThreads) k_cg_step(T* __restrict__ x, T* __restrict__ p, const T* __restrict__ r,
+                                                         const T* __restrict__ dinv, double* __restrict__ sc, int cur,
+                                                         const double* __restrict__ rz_part,
+                                                         const double* __restrict__ rr_part, int64_t n,
+                                                         const int* __restrict__ flag, double* __restrict__ host) {
+  __shared__ double sh[kRedThreads];
+  const double rzn = sum_partials(rz_part, gridDim.x, sh);
+  const double rz = sc[cur];
+  const T alpha = T(sc[3]), beta = T(rz != 0.0 ? rzn / rz : 0.0);
+  if (blockIdx.x == 0) {
+    const double rr = sum_partials(rr_part, gridDim.x, sh);
+    if (threadIdx.x == 0) {
+      sc[1 - cur] = rzn;
+      sc[5] = rr;
+      if (host) {
+        host[5] = rr;
+        host[8] = double(*flag);
+      }
+    }
+  }
+  for (int64_t i = int64_t(blockIdx.x) * kRedThreads + threadIdx.x; i < n; i += int64_t(kRedBlocks) * kRedThreads) {
+    const T pi = p[i];
+    x[i] = std::fma(alpha, pi, x[i]);
+    p[i] = std::fma(beta, pi, r[i] * dinv[i]);
+  }
 }
 
-// start of a PCG solve on A x = r (r already holds the right-hand side): x = 0, z = r/diag, p = z;
-// partials of r.z and r.r
+// start of a PCG solve on A x = r (r already holds the right-hand side): x = 0, p = z = r/diag;
+// partials of r.z
 template <class T>
-__global__ void __launch_bounds__(kRedThreads) k_cg_start(T* __restrict__ x, T* __restrict__ r, T* __restrict__ z,
+__global__ void __launch_bounds__(kRedThreads) k_cg_start(T* __restrict__ x, const T* __restrict__ r,
                                                           T* __restrict__ p, const T* __restrict__ dinv, int64_t n,
                                                           double* __restrict__ part) {
   __shared__ double sh[kRedThreads];
-  double srz = 0.0, srr = 0.0;
+  double srz = 0.0;
   for (int64_t i = int64_t(blockIdx.x) * kRedThreads + threadIdx.x; i < n; i += int64_t(kRedBlocks) * kRedThreads) {
     const T ri = r[i];
     x[i] = T(0);
     const T zi = ri * dinv[i];
-    z[i] = zi;
     p[i] = zi;
     srz += double(ri) * double(zi);
-    srr += double(ri) * double(ri);
   }
   srz = block_sum(srz, sh);
-  srr = block_sum(srr, sh);
-  if (threadIdx.x == 0) {
-    part[blockIdx.x] = srz;
-    part[kRedBlocks + blockIdx.x] = srr;
-  }
+  if (threadIdx.x == 0) part[blockIdx.x] = srz;
 }
 
 // r64 = b - Ax (FP64); rs = r64 * scale (FP32 or FP64 inner copy); partial of r.r
@@ -247,6 +370,11 @@ __global__ void k_nonfinite(const double* __restrict__ a, int64_t n, int* __rest
     if (!isfinite(a[i])) *flag = 1;
 }
 
+__global__ void k_report(const double* __restrict__ sc, const int* __restrict__ flag, double* __restrict__ host) {
+  if (threadIdx.x < 8) host[threadIdx.x] = sc[threadIdx.x];
+  if (threadIdx.x == 8) host[8] = double(*flag);
+}
+
 static dim3 grid_for(int64_t n, int threads = 256) {
   int64_t b = (n + threads - 1) / threads;
   if (b > 65536) b = 65536;
@@ -273,28 +401,28 @@ struct nir_cg_plan {
   double lambda = 0;
   int64_t nl = 0, ng = 0;
   // FP64 vectors
-  // outer (FP64): solution xs, right-hand side, A xs, residual; inner FP64 set d, r, z, p, Ap
+  // outer (FP64): solution xs, right-hand side, A xs, residual; inner FP64 set d, r, p, Ap
   double *xl = nullptr, *yl = nullptr, *bvec = nullptr, *xs = nullptr, *rout = nullptr, *Ax = nullptr, *d = nullptr,
-         *r = nullptr, *z = nullptr, *p = nullptr, *Ap = nullptr, *dinv = nullptr, *diag = nullptr;
+         *r = nullptr, *p = nullptr, *Ap = nullptr, *dinv = nullptr, *diag = nullptr;
   // inner FP32 set
-  float *xl32 = nullptr, *yl32 = nullptr, *d32 = nullptr, *r32 = nullptr, *z32 = nullptr, *p32 = nullptr,
+  float *xl32 = nullptr, *yl32 = nullptr, *d32 = nullptr, *r32 = nullptr, *p32 = nullptr,
         *Ap32 = nullptr, *dinv32 = nullptr;
-  double* part = nullptr;    // 2 * kRedBlocks
-  double* sc = nullptr;      // scalars: 0 rz, 1 rz_new, 2 pAp, 3 alpha, 4 beta, 5 rr, 6 ||r||^2 (outer), 7 bb
+  double* part = nullptr;    // 3 * kRedBlocks: p.Ap (and single reductions), r.z, r.r
+  double* sc = nullptr;      // scalars: 0, 1 r.z (current and next in turn), 2 pAp, 3 alpha, 5 rr, 6 ||r||^2 (outer), 7 bb
   int* flag = nullptr;
   hipStream_t cap = nullptr;
   hipGraphExec_t g_iter64 = nullptr, g_iter32 = nullptr, g_iter16 = nullptr;
   bool f16split = false;      // inner FP32 apply with FP16-split MFMA contractions
   int k_per_graph = 10;
-  double* host_sc = nullptr;  // pinned
+  double* host_sc = nullptr;  // pinned: the scalars, then the breakdown flag
 };
 
 namespace nir {
 
-static nir_status apply_local(nir_cg_plan* pl, int dtype, hipStream_t s, const void* xg, void* yg) {
-  // (gather ->) element apply -> scatter-reduce.  The hex pencil kernels gather by themselves: 32^3
-  // hexahedra at P = 6 in FP32, 25.0 us of a gather's own pass (57 MB written and read again) and a
-  // launch become 6 us of the apply (74.9 -> 80.9 us)
+// the element results of A x, in yl (FP64) or yl32: (gather ->) element apply.  The hex pencil
+// kernels gather by themselves: 32^3 hexahedra at P = 6 in FP32, 25.0 us of a gather's own pass
+// (57 MB written and read again) and a launch become 6 us of the apply (74.9 -> 80.9 us)
+static nir_status apply_elements(nir_cg_plan* pl, int dtype, hipStream_t s, const void* xg) {
   const nir_assembly* A = pl->A;
   const bool own = helm_gathers(pl->basis, dtype) && !(dtype == NIR_F32 && pl->f16split);
   OpArgs a{};
@@ -312,8 +440,6 @@ static nir_status apply_local(nir_cg_plan* pl, int dtype, hipStream_t s, const v
     a.out0 = pl->yl;
     a.helm = pl->g64.helm;
     NIR_TRYS(launch_helm_auto(pl->basis, NIR_F64, pl->b64.deformed, a, s));
-    hipLaunchKernelGGL(k_scatter<double>, grid_for(pl->ng), dim3(256), 0, s, A->off, A->idx, pl->yl,
-                       static_cast<double*>(yg), pl->ng);
   } else {
     if (own) {
       a.in0 = xg;
@@ -329,34 +455,47 @@ static nir_status apply_local(nir_cg_plan* pl, int dtype, hipStream_t s, const v
       NIR_TRYS(launch_helm_hex_f16split(pl->basis, pl->b64.deformed, a, s));
     else
       NIR_TRYS(launch_helm_auto(pl->basis, NIR_F32, pl->b64.deformed, a, s));
-    hipLaunchKernelGGL(k_scatter<float>, grid_for(pl->ng), dim3(256), 0, s, A->off, A->idx, pl->yl32,
-                       static_cast<float*>(yg), pl->ng);
   }
   return hip_check(hipGetLastError(), "assembled apply launch");
 }
 
-// one PCG iteration on the vectors of the given precision (device-side alpha/beta)
+// blocks of a reduction over n values, as of every kernel that sums its partials: those past them
+// would have no value (their partials are zero)
+static dim3 red_grid(int64_t n) { return dim3(unsigned(std::min<int64_t>(kRedBlocks, (n + kRedThreads - 1) / kRedThreads))); }
+
+// sc[dst] = a . b (the k_dot_part partials in `part`)
+static void launch_final(nir_cg_plan* pl, hipStream_t s, const double* part, int dst) {
+  hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, s, part, int(red_grid(pl->ng).x), pl->sc, dst);
+}
+
+// one PCG iteration on the vectors of the given precision (device-side alpha/beta); `cur` is the
+// slot of r.z, `host` where the last iteration of a graph leaves r.r and the flag
 template <class T>
-static nir_status pcg_iteration(nir_cg_plan* pl, hipStream_t s, T* x, T* r, T* z, T* p, T* Ap, const T* dinv) {
-  const int dt = sizeof(T) == 8 ? NIR_F64 : NIR_F32;
-  NIR_TRYS(apply_local(pl, dt, s, p, Ap));
-  hipLaunchKernelGGL((k_dot_part<T, T>), dim3(kRedBlocks), dim3(kRedThreads), 0, s, p, Ap, pl->ng, pl->part);
-  hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, s, pl->part, 1, pl->sc, 2, 1, pl->flag);
-  hipLaunchKernelGGL((k_cg_update<T>), dim3(kRedBlocks), dim3(kRedThreads), 0, s, x, r, z, p, Ap, dinv, pl->sc, pl->ng,
-                     pl->part);
-  // rz_new -> sc[1], rr -> sc[2]... rr goes to sc[5]: two finals keep the slot layout simple
-  hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, s, pl->part + kRedBlocks, 1, pl->sc, 5, 0, pl->flag);
-  hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, s, pl->part, 1, pl->sc, 1, 2, pl->flag);
-  hipLaunchKernelGGL((k_cg_pupdate<T>), grid_for(pl->ng), dim3(256), 0, s, p, z, pl->sc, pl->ng);
+static nir_status pcg_iteration(nir_cg_plan* pl, hipStream_t s, T* x, T* r, T* p, T* Ap, const T* dinv, int cur,
+                                double* host) {
+  const nir_assembly* A = pl->A;
+  const T* yl;
+  if constexpr (sizeof(T) == 8) yl = pl->yl; else yl = pl->yl32;
+  const dim3 grid = red_grid(pl->ng), block(kRedThreads);
+  double *pap = pl->part, *rz = pl->part + kRedBlocks, *rr = pl->part + 2 * kRedBlocks;
+  NIR_TRYS(apply_elements(pl, sizeof(T) == 8 ? NIR_F64 : NIR_F32, s, p));
+  if (pl->ng > int64_t(kRedBlocks) * kRedThreads)
+    hipLaunchKernelGGL((k_cg_scatter<T, 4>), grid, dim3(4 * kRedThreads), 0, s, A->off, A->idx, yl, p, Ap, pl->ng, pap);
+  else   // one row per lane
+    hipLaunchKernelGGL((k_cg_scatter<T, 1>), grid, block, 0, s, A->off, A->idx, yl, p, Ap, pl->ng, pap);
+  hipLaunchKernelGGL((k_cg_residual<T>), grid, block, 0, s, r, Ap, dinv, pl->sc, cur, pap, pl->ng, rz, rr, pl->flag);
+  hipLaunchKernelGGL((k_cg_step<T>), grid, block, 0, s, x, p, r, dinv, pl->sc, cur, rz, rr, pl->ng, pl->flag, host);
   return hip_check(hipGetLastError(), "CG iteration launch");
 }
 
 template <class T>
-static nir_status capture_iters(nir_cg_plan* pl, hipGraphExec_t* exec, T* x, T* r, T* z, T* p, T* Ap, const T* dinv) {
+static nir_status capture_iters(nir_cg_plan* pl, hipGraphExec_t* exec, T* x, T* r, T* p, T* Ap, const T* dinv) {
   hipGraph_t g = nullptr;
   NIR_TRYS(hip_check(hipStreamBeginCapture(pl->cap, hipStreamCaptureModeThreadLocal), "begin capture"));
   nir_status st = NIR_OK;
-  for (int k = 0; k < pl->k_per_graph && st == NIR_OK; ++k) st = pcg_iteration<T>(pl, pl->cap, x, r, z, p, Ap, dinv);
+  const int n = pl->k_per_graph;   // even: the next graph starts at slot 0 again
+  for (int k = 0; k < n && st == NIR_OK; ++k)
+    st = pcg_iteration<T>(pl, pl->cap, x, r, p, Ap, dinv, k & 1, k == n - 1 ? pl->host_sc : nullptr);
   const nir_status st2 = hip_check(hipStreamEndCapture(pl->cap, &g), "end capture");
   if (st != NIR_OK) return st;
   if (st2 != NIR_OK) return st2;
@@ -365,19 +504,21 @@ static nir_status capture_iters(nir_cg_plan* pl, hipGraphExec_t* exec, T* x, T* 
   return st;
 }
 
-// start PCG on A x = r (x = 0); sc[0] = r.z, sc[5] = r.r
+// start PCG on A x = r (x = 0); sc[0] = r.z
 template <class T>
-static nir_status pcg_start(nir_cg_plan* pl, hipStream_t s, T* x, T* r, T* z, T* p, const T* dinv) {
-  hipLaunchKernelGGL((k_cg_start<T>), dim3(kRedBlocks), dim3(kRedThreads), 0, s, x, r, z, p, dinv, pl->ng, pl->part);
-  hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, s, pl->part, 1, pl->sc, 0, 0, pl->flag);
-  hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, s, pl->part + kRedBlocks, 1, pl->sc, 5, 0, pl->flag);
+static nir_status pcg_start(nir_cg_plan* pl, hipStream_t s, T* x, T* r, T* p, const T* dinv) {
+  hipLaunchKernelGGL((k_cg_start<T>), red_grid(pl->ng), dim3(kRedThreads), 0, s, x, r, p, dinv, pl->ng, pl->part);
+  launch_final(pl, s, pl->part, 0);
   return hip_check(hipGetLastError(), "CG start launch");
 }
 
+// the scalars and the flag into host_sc (pinned), synchronously
 static nir_status read_scalars(nir_cg_plan* pl, hipStream_t s, int* flag) {
-  NIR_TRYS(hip_check(hipMemcpyAsync(pl->host_sc, pl->sc, 8 * sizeof(double), hipMemcpyDeviceToHost, s), "copy scalars"));
-  NIR_TRYS(hip_check(hipMemcpyAsync(flag, pl->flag, sizeof(int), hipMemcpyDeviceToHost, s), "copy flag"));
-  return hip_check(hipStreamSynchronize(s), "stream sync");
+  hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, s, pl->sc, pl->flag, pl->host_sc);
+  NIR_TRYS(hip_check(hipGetLastError(), "scalar report launch"));
+  NIR_TRYS(hip_check(hipStreamSynchronize(s), "stream sync"));
+  *flag = pl->host_sc[8] != 0.0;
+  return NIR_OK;
 }
 
 }  // namespace nir
@@ -565,16 +706,16 @@ nir_status nir_cg_plan_create(const nir_batch* b64, const nir_basis* basis, cons
   };
   const size_t nl = size_t(pl->nl), ng = size_t(pl->ng);
   al((void**)&pl->xl, nl * 8); al((void**)&pl->yl, nl * 8);
-  for (double** v : {&pl->bvec, &pl->xs, &pl->rout, &pl->Ax, &pl->d, &pl->r, &pl->z, &pl->p, &pl->Ap, &pl->dinv, &pl->diag})
+  for (double** v : {&pl->bvec, &pl->xs, &pl->rout, &pl->Ax, &pl->d, &pl->r, &pl->p, &pl->Ap, &pl->dinv, &pl->diag})
     al((void**)v, ng * 8);
   if (helm32) {
     al((void**)&pl->xl32, nl * 4); al((void**)&pl->yl32, nl * 4);
-    for (float** v : {&pl->d32, &pl->r32, &pl->z32, &pl->p32, &pl->Ap32, &pl->dinv32}) al((void**)v, ng * 4);
+    for (float** v : {&pl->d32, &pl->r32, &pl->p32, &pl->Ap32, &pl->dinv32}) al((void**)v, ng * 4);
   }
-  al((void**)&pl->part, 2 * kRedBlocks * 8);
+  al((void**)&pl->part, 3 * kRedBlocks * 8);
   al((void**)&pl->sc, 8 * 8);
   al((void**)&pl->flag, sizeof(int));
-  if (st == NIR_OK) st = hip_check(hipHostMalloc((void**)&pl->host_sc, 8 * 8, hipHostMallocDefault), "pinned alloc");
+  if (st == NIR_OK) st = hip_check(hipHostMalloc((void**)&pl->host_sc, 9 * 8, hipHostMallocDefault), "pinned alloc");
   if (st == NIR_OK) st = hip_check(hipStreamCreateWithFlags(&pl->cap, hipStreamNonBlocking), "stream create");
   if (st != NIR_OK) {
     nir_cg_plan_destroy(pl);
@@ -604,8 +745,8 @@ nir_status nir_cg_plan_destroy(nir_cg_plan* pl) {
   if (pl->g_iter32) (void)hipGraphExecDestroy(pl->g_iter32);
   if (pl->g_iter16) (void)hipGraphExecDestroy(pl->g_iter16);
   for (void* v : {(void*)pl->xl, (void*)pl->yl, (void*)pl->bvec, (void*)pl->xs, (void*)pl->rout, (void*)pl->Ax,
-                  (void*)pl->d, (void*)pl->r, (void*)pl->z, (void*)pl->p, (void*)pl->Ap, (void*)pl->dinv,
-                  (void*)pl->diag, (void*)pl->xl32, (void*)pl->yl32, (void*)pl->d32, (void*)pl->r32, (void*)pl->z32,
+                  (void*)pl->d, (void*)pl->r, (void*)pl->p, (void*)pl->Ap, (void*)pl->dinv,
+                  (void*)pl->diag, (void*)pl->xl32, (void*)pl->yl32, (void*)pl->d32, (void*)pl->r32,
                   (void*)pl->p32, (void*)pl->Ap32, (void*)pl->dinv32, (void*)pl->part, (void*)pl->sc, (void*)pl->flag})
     if (v) (void)hipFree(v);
   if (pl->host_sc) (void)hipHostFree(pl->host_sc);
@@ -633,9 +774,9 @@ nir_status nir_cg_solve(nir_cg_plan* pl, int32_t mode, const double* b, double* 
   NIR_TRYS(hip_check(hipMemsetAsync(pl->flag, 0, sizeof(int), s), "clear flag"));
   hipLaunchKernelGGL(k_nonfinite, grid_for(ng), dim3(256), 0, s, pl->bvec, ng, pl->flag);
   hipLaunchKernelGGL(k_nonfinite, grid_for(ng), dim3(256), 0, s, pl->xs, ng, pl->flag);
-  hipLaunchKernelGGL((k_dot_part<double, double>), dim3(kRedBlocks), dim3(kRedThreads), 0, s, pl->bvec, pl->bvec, ng,
+  hipLaunchKernelGGL((k_dot_part<double, double>), red_grid(ng), dim3(kRedThreads), 0, s, pl->bvec, pl->bvec, ng,
                      pl->part);
-  hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, s, pl->part, 1, pl->sc, 7, 0, pl->flag);
+  launch_final(pl, s, pl->part, 7);
   NIR_TRYS(read_scalars(pl, s, &flag));
   if (flag) return fail(NIR_ENONFINITE, "b or x0 holds a NaN or Inf");
   const double bnorm = std::sqrt(pl->host_sc[7]);
@@ -647,10 +788,11 @@ nir_status nir_cg_solve(nir_cg_plan* pl, int32_t mode, const double* b, double* 
     // iterative refinement: r = b - A x in FP64, inner PCG on A d = r/||r|| (FP64 or FP32),
     // x += ||r|| d; plain FP64 CG is the case whose inner solve runs to the final tolerance
     for (;;) {
-      NIR_TRYS(apply_local(pl, NIR_F64, s, pl->xs, pl->Ax));
-      hipLaunchKernelGGL(k_residual<double>, dim3(kRedBlocks), dim3(kRedThreads), 0, s, pl->bvec, pl->Ax, pl->rout,
+      NIR_TRYS(apply_elements(pl, NIR_F64, s, pl->xs));
+      hipLaunchKernelGGL(k_scatter<double>, grid_for(ng), dim3(256), 0, s, pl->A->off, pl->A->idx, pl->yl, pl->Ax, ng);
+      hipLaunchKernelGGL(k_residual<double>, red_grid(ng), dim3(kRedThreads), 0, s, pl->bvec, pl->Ax, pl->rout,
                          ng, pl->part);
-      hipLaunchKernelGGL(k_final, dim3(1), dim3(kRedThreads), 0, s, pl->part, 1, pl->sc, 6, 0, pl->flag);
+      launch_final(pl, s, pl->part, 6);
       NIR_TRYS(read_scalars(pl, s, &flag));
       const double rn = std::sqrt(pl->host_sc[6]);
       inf.rel_residual = rn / bnorm;
@@ -662,21 +804,21 @@ nir_status nir_cg_solve(nir_cg_plan* pl, int32_t mode, const double* b, double* 
       const double target = mode == NIR_CG_FP64 ? need : std::max(inner_rtol, need);
       if (mode == NIR_CG_FP64) {
         hipLaunchKernelGGL(k_scale_down<double>, grid_for(ng), dim3(256), 0, s, pl->rout, pl->r, pl->sc, ng);
-        NIR_TRYS(pcg_start<double>(pl, s, pl->d, pl->r, pl->z, pl->p, pl->dinv));
-        if (!pl->g_iter64) NIR_TRYS(capture_iters<double>(pl, &pl->g_iter64, pl->d, pl->r, pl->z, pl->p, pl->Ap, pl->dinv));
+        NIR_TRYS(pcg_start<double>(pl, s, pl->d, pl->r, pl->p, pl->dinv));
+        if (!pl->g_iter64) NIR_TRYS(capture_iters<double>(pl, &pl->g_iter64, pl->d, pl->r, pl->p, pl->Ap, pl->dinv));
       } else {
         hipLaunchKernelGGL(k_scale_down<float>, grid_for(ng), dim3(256), 0, s, pl->rout, pl->r32, pl->sc, ng);
-        NIR_TRYS(pcg_start<float>(pl, s, pl->d32, pl->r32, pl->z32, pl->p32, pl->dinv32));
+        NIR_TRYS(pcg_start<float>(pl, s, pl->d32, pl->r32, pl->p32, pl->dinv32));
         hipGraphExec_t* gx = pl->f16split ? &pl->g_iter16 : &pl->g_iter32;
-        if (!*gx) NIR_TRYS(capture_iters<float>(pl, gx, pl->d32, pl->r32, pl->z32, pl->p32, pl->Ap32, pl->dinv32));
+        if (!*gx) NIR_TRYS(capture_iters<float>(pl, gx, pl->d32, pl->r32, pl->p32, pl->Ap32, pl->dinv32));
       }
       bool broke = false;
       while (inf.inner_iters < maxit) {
         NIR_TRYS(hip_check(hipGraphLaunch(mode == NIR_CG_FP64 ? pl->g_iter64
                                           : (pl->f16split ? pl->g_iter16 : pl->g_iter32), s), "graph launch"));
         inf.inner_iters += pl->k_per_graph;
-        NIR_TRYS(read_scalars(pl, s, &flag));
-        if (flag) { broke = true; break; }
+        NIR_TRYS(hip_check(hipStreamSynchronize(s), "stream sync"));   // r.r and the flag are in host_sc
+        if (pl->host_sc[8] != 0.0) { broke = true; break; }
         if (!(std::sqrt(pl->host_sc[5]) > target)) break;
       }
       if (broke) {
