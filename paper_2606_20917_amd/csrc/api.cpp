@@ -284,16 +284,16 @@ nir_status nir_basis_create(int32_t shape, int32_t P, int32_t Q, nir_basis** out
   fill(b->t32, d32);
   {
     const int Q = b->Q, P = b->P;
-    // [point][mode] direction-1 rows, then (hexahedra) the even-odd folded rows: for the point
+    // [point][mode] direction-1 rows, then the even-odd folded rows (eo_fold.h): for the point
     // pair (h, Q-1-h), h < ceil(Q/2), 2P values ((B0+B1)/2, B2, B4, .. | (B0-B1)/2, B3, B5, ..
     // | the same of B'); the Gauss-Lobatto points are symmetric and psi^a_0(-z) = psi^a_1(z),
     // psi^a_p(-z) = (-1)^p psi^a_p(z) for p >= 2.  On a middle point (odd Q) the odd half of B
     // and the even half of B' vanish and are stored as exact zeros.
-    const int H = (Q + 1) / 2, NE = 1 + (P - 1) / 2, neo = b->shape == kHex && Q == P + 1 ? H * 2 * P : 0;
-    // collapsed shapes: the forward sweeps' factors in [slice][point][term] order (col_a_off,
-    // col_b_off), values then derivatives
+    const int H = (Q + 1) / 2, NE = 1 + (P - 1) / 2, neo = H * 2 * P;
+    // collapsed shapes: the factors of sweep A and, for the tetrahedron, of sweep B in
+    // [slice][point][term] order (col_a_off, col_b_off), values then derivatives
     const bool col = b->shape != kHex && Q == P + 1;
-    const int na = col ? col_a_off(b->shape, P, P) : 0, nbt = col ? col_b_off(b->shape, P, P) : 0;
+    const int na = col ? col_a_off(b->shape, P, P) : 0, nbt = b->shape == kTet ? col_b_off(b->shape, P, P) : 0;
     std::vector<double> p64(2 * Q * P + neo + 2 * na + 2 * nbt);
     std::vector<float> p32(p64.size());
     auto B = [&](int i, int p) { return b->host.T1[p * Q + i]; };
@@ -303,7 +303,7 @@ nir_status nir_basis_create(int32_t shape, int32_t P, int32_t Q, nir_basis** out
         p64[i * P + p] = B(i, p);
         p64[Q * P + i * P + p] = Dd(i, p);
       }
-    for (int h = 0; neo && h < H; ++h) {
+    for (int h = 0; h < H; ++h) {
       double* r = p64.data() + 2 * Q * P + h * 2 * P;
       const bool mid = 2 * h == Q - 1;
       r[0] = 0.5 * (B(h, 0) + B(h, 1));
@@ -337,11 +337,10 @@ nir_status nir_basis_create(int32_t shape, int32_t P, int32_t Q, nir_basis** out
           }
         }
       }
-      for (int p = 0; p < P; ++p) {
+      for (int p = 0; p < P && sh == kTet; ++p) {
         const int nt = col_b_terms(sh, P, p), off = col_b_off(sh, P, p);
-        const int nq = sh == kTet ? P - p : P;
         for (int q = 0; q < nt; ++q) {
-          const int pr = q < nq ? col_pair(sh, P, p, q) : col_pair(sh, P, 0, 1);   // tet p = 1: pair (0,1)
+          const int pr = q < P - p ? col_pair(sh, P, p, q) : col_pair(sh, P, 0, 1);   // p = 1: pair (0,1)
           for (int j = 0; j < Q; ++j) {
             B2[off + j * nt + q] = b->host.T2[pr * Q + j];
             dB2[off + j * nt + q] = b->host.dT2[pr * Q + j];
@@ -360,10 +359,8 @@ nir_status nir_basis_create(int32_t shape, int32_t P, int32_t Q, nir_basis** out
     }
     b->pencil64 = static_cast<const double*>(b->devpencil);
     b->pencil32 = reinterpret_cast<const float*>(static_cast<const char*>(b->devpencil) + nb64);
-    if (neo) {
-      b->eo64 = b->pencil64 + 2 * Q * P;
-      b->eo32 = b->pencil32 + 2 * Q * P;
-    }
+    b->t64.eo = b->eo64 = b->pencil64 + 2 * Q * P;
+    b->t32.eo = b->eo32 = b->pencil32 + 2 * Q * P;
     if (col) {
       const size_t o = size_t(2 * Q * P + neo);
       b->t64.T3t = b->pencil64 + o;

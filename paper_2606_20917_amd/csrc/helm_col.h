@@ -6,18 +6,15 @@
 
 namespace nir {
 
-// Register budget, as waves per SIMD requested from the compiler, so that registers do not hold
-// the occupancy below what LDS allows.  LDS (160 KiB per CU) admits k blocks of NW wavefronts
-// (at least P: one per slice).  A block's wavefronts take ceil(NW/4) slots on some SIMD, so k
-// blocks need k ceil(NW/4) waves per SIMD there, not the k NW / 4 the compiler counts, and the
-// compiler grants no more than its own count, ceil(k NW / 4).  Measured on MI355X: a second
-// 7-wavefront FP64 group at P = 6 fits only at 128 VGPRs (pyr24 11.7 -> 16.0 GDoF/s, deformed
-// tets 8.2 -> 10.1, no spills); three 8-wavefront FP32 tet groups at P = 7 only at 80 (20.9 ->
-// 24.1).  Capped at 4 waves in FP64, where prisms at P = 8 gain a third from 4 (40 B of spills),
-// and in FP32 to P = 4, where 8 gained nothing and cost 4 %.  Kernels with per-element factors
-// keep the total-waves count (affine prisms at P = 7 spill 50 registers at 128 and run 5 %
-// slower), and the affine tetrahedron the compiler's own budget (it lost a third with the
-// prism's at P = 8).
+// Register budget of the operator kernels and of affine batches, as waves per SIMD requested from
+// the compiler, so that registers do not hold the occupancy below what LDS allows.  LDS (160 KiB
+// per CU) admits k blocks of NW wavefronts (at least P: one per slice).  A block's wavefronts take
+// ceil(NW/4) slots on some SIMD, so k blocks need k ceil(NW/4) waves per SIMD there, not the k NW / 4
+// the compiler counts, and the compiler grants no more than its own count, ceil(k NW / 4), while
+// the LDS is static.  Capped at 4 waves in FP64 and in FP32 to P = 4, where 8 gained nothing and
+// cost 4 %.  Kernels with per-element factors keep the total-waves count (affine prisms at P = 7
+// spill 50 registers at 128 and run 5 % slower), and the affine tetrahedron the compiler's own
+// budget (it lost a third with the prism's at P = 8).
 template <int SHAPE, int P, class T, bool DEF = true, int OPM = 0>
 constexpr int col_waves_target() {
   using D = ColDims<SHAPE, P, T, 0, OPM>;
@@ -30,43 +27,78 @@ constexpr int col_waves_target() {
   return waves < 1 ? 1 : (waves > cap ? cap : waves);
 }
 
+// Launch shape of the Helmholtz apply with per-point factors: elements per group (0: ColDims' rule)
+// and the register budget W, in waves per SIMD.  The LDS is dynamic, so that the compiler grants
+// the W asked for whatever the group's LDS: the groups that share a CU fill its SIMDs unevenly
+// (ceil(NW/4) slots on one of them), which it does not count.  From a sweep of E, W and the planes
+// kept in LDS on MI355X (24^3 cubes, lambda = 1), start of the sweep -> chosen:
+//   FP64 tetrahedra and pyramids at P = 7: 7 elements, two groups per CU at 128 VGPRs, against 8
+//        elements and one group: 697 -> 582 and 768 -> 617 us; prisms at P = 5: 8 elements in 5
+//        wavefronts instead of 10 in 6: 90.0 -> 87.7 us; P = 2: 13 elements in 2 wavefronts (FP64
+//        pyramids 36.4 -> 29.4 us with the first factors requested after sweep B)
+//   W in FP64: the compiler's own allocation (W = 2) fits two or three groups at P = 5, 6 and, on
+//        prisms, P = 8 and is 1-5 % faster than one forced to 128 VGPRs (prisms at P = 8: 298.5
+//        -> 290.4 us); P = 7 needs the 128 of W = 4 for its two groups
+//   W in FP32: 80 VGPRs (W = 6) let a second group of 9 or 10 wavefronts in at P = 9 and, on prisms,
+//        P = 10: 322 -> 252, 1060 -> 767 (tetrahedra 959 -> 766) and 414 -> 343 us; tetrahedra and
+//        pyramids at P = 10 spill there (678 -> 850 us) and keep one group
+struct ColCfg {
+  int E, W;
+};
+template <int SHAPE, int P, class T>
+constexpr ColCfg col_cfg() {
+  constexpr bool VTX = SHAPE != kPrism;
+  //                        P =  2  3  4  5  6  7  8  9  10
+  constexpr int w64[2][9] = {{5, 5, 4, 4, 2, 4, 2, 3, 3},    // prisms
+                             {5, 5, 4, 2, 2, 4, 3, 3, 3}};   // tetrahedra and pyramids
+  constexpr int w32[2][9] = {{8, 8, 8, 8, 8, 6, 6, 3, 6}, {8, 8, 8, 8, 4, 6, 6, 6, 3}};
+  int e = P == 2 ? 13 : 0;
+  if (sizeof(T) == 8 && P == 7 && VTX) e = 7;
+  if (sizeof(T) == 8 && P == 5 && !VTX) e = 8;
+  int w = sizeof(T) == 8 ? w64[VTX][P - 2] : w32[VTX][P - 2];
+  if (sizeof(T) == 8 && SHAPE == kPyr && P == 4) w = 5;   // 156 -> 130 us
+  return ColCfg{e, w};
+}
+
 template <int SHAPE, int P, class T, bool DEF>
-__global__ void __launch_bounds__((ColDims<SHAPE, P, T>::BLOCK))
-__attribute__((amdgpu_waves_per_eu(col_waves_target<SHAPE, P, T, DEF>())))
+using ColKernelDims = ColDims<SHAPE, P, T, DEF ? col_cfg<SHAPE, P, T>().E : 0>;
+
+template <int SHAPE, int P, class T, bool DEF>
+__global__ void __launch_bounds__((ColKernelDims<SHAPE, P, T, DEF>::BLOCK))
+__attribute__((amdgpu_waves_per_eu(DEF ? col_cfg<SHAPE, P, T>().W : col_waves_target<SHAPE, P, T, false>())))
     k_helm_col(DevTab<T> tb, const T* __restrict__ pen, const T* __restrict__ x, T* __restrict__ y,
                const T* __restrict__ helm, T lambda, int64_t nelmt) {
-  using D = ColDims<SHAPE, P, T>;
-  __shared__ T lds[D::LDS];
-  helm_col_group<SHAPE, P, T, DEF>(tb, pen, x, y, helm, lambda, nelmt, int64_t(blockIdx.x) * D::E, lds);
+  using D = ColKernelDims<SHAPE, P, T, DEF>;
+  extern __shared__ double dyn[];   // D::LDS values of T
+  helm_col_group<SHAPE, P, T, DEF, D::E>(tb, pen, x, y, helm, lambda, nelmt, int64_t(blockIdx.x) * D::E,
+                                         reinterpret_cast<T*>(dyn));
+}
+
+template <int SHAPE, int P, class T, bool DEF>
+nir_status launch_col_cfg(const DevTab<T>& tb, const T* pen, const OpArgs& a, hipStream_t s) {
+  using D = ColKernelDims<SHAPE, P, T, DEF>;
+  static_assert(D::LDS * sizeof(T) <= 160 * 1024, "LDS budget");
+  const int64_t nb = (a.nelmt + D::E - 1) / D::E;
+  if (nb > 0x7fffffff) return fail(NIR_EINVAL, "too many elements for one launch");
+  if (nb == 0) return ok();
+  hipLaunchKernelGGL((k_helm_col<SHAPE, P, T, DEF>), dim3(unsigned(nb)), dim3(D::BLOCK), D::LDS * sizeof(T), s, tb, pen,
+                     static_cast<const T*>(a.in0), static_cast<T*>(a.out0), static_cast<const T*>(a.helm),
+                     T(a.lambda), a.nelmt);
+  return hip_check(hipGetLastError(), "collapsed Helmholtz launch");
 }
 
 template <int SHAPE, int P, class T>
 nir_status launch_col_PT(const nir_basis* b, int deformed, const OpArgs& a, hipStream_t s) {
-  using D = ColDims<SHAPE, P, T>;
-  static_assert(D::LDS * sizeof(T) <= D::LDS_BYTES, "LDS budget");
-  DevTab<T> tb;
+  const DevTab<T>* tb;
   const T* pen;
   if constexpr (sizeof(T) == 8) {
-    tb = b->t64;
+    tb = &b->t64;
     pen = b->pencil64;
   } else {
-    tb = b->t32;
+    tb = &b->t32;
     pen = b->pencil32;
   }
-  const int64_t nb = (a.nelmt + D::E - 1) / D::E;
-  if (nb > 0x7fffffff) return fail(NIR_EINVAL, "too many elements for one launch");
-  if (nb == 0) return ok();
-  const T* x = static_cast<const T*>(a.in0);
-  T* y = static_cast<T*>(a.out0);
-  const T* helm = static_cast<const T*>(a.helm);
-  const dim3 grid(static_cast<unsigned>(nb)), block(D::BLOCK);
-  if (deformed)
-    hipLaunchKernelGGL((k_helm_col<SHAPE, P, T, true>), grid, block, 0, s, tb, pen, x, y, helm, T(a.lambda),
-                       a.nelmt);
-  else
-    hipLaunchKernelGGL((k_helm_col<SHAPE, P, T, false>), grid, block, 0, s, tb, pen, x, y, helm, T(a.lambda),
-                       a.nelmt);
-  return hip_check(hipGetLastError(), "collapsed Helmholtz launch");
+  return deformed ? launch_col_cfg<SHAPE, P, T, true>(*tb, pen, a, s) : launch_col_cfg<SHAPE, P, T, false>(*tb, pen, a, s);
 }
 
 template <int SHAPE>

@@ -33,6 +33,15 @@
 //        pairs (sl, 0..sl) and (0..sl-1, sl), each with P - sl terms; B and C are the prism's
 //        (psi^a_q in eta2, psi^a_p in eta1), with both eta1 and eta2 collapsed in the chain rule.
 //
+// The contractions over Gauss-Lobatto points are folded by even-odd symmetry (eo_fold.h): B and B^T
+// of the prism and the pyramid, and C and C^T of affine elements.  With per-point factors C stays
+// unfolded: a pair of points holds twice the factors and values, about 30 FP64 registers more, and
+// the spills cost more than the arithmetic saved (tetrahedra at P = 6 in FP64 420 -> 663 us).  What
+// bounds it there is the factor stream against the sweeps that stream nothing, hence the first
+// point's factors in flight through A and B and buffer loads without address arithmetic.  24^3
+// cubes, FP64, before and after: prisms at P = 8 370 -> 287 us (3.4 -> 4.4 TB/s), at P = 10 824 ->
+// 642; pyramids at P = 5 321 -> 289, at P = 7 866 -> 617; tetrahedra at P = 7 749 -> 576 us.
+//
 // LDS per element (values of T): one region of 3 P Q^2 values that holds, in turn, the
 // coefficients, the A rows, the B planes, the C^T planes, the B^T rows and the results;
 // every stage reads its inputs into registers, synchronises, then writes its outputs.  The
@@ -41,6 +50,7 @@
 
 #include <type_traits>
 
+#include "eo_fold.h"
 #include "nir_internal.h"
 #include "uniform_table.h"
 
@@ -146,6 +156,27 @@ struct ColUnit {
   T* L;
 };
 
+// Planes of sweep C that stay in LDS through the point loop (P reads again at every point or point
+// pair) instead of taking 2P (FP64) or P (FP32) registers each: 0 none, 1 the third, 2 the second
+// and the third.  Per-point factors: the third in FP64 (prisms at P = 8 with two groups per CU at
+// 128 VGPRs: 527 us with none, spilling, 312 with the third, 321 with both) and in FP32 where the
+// budget of the launch would spill otherwise (P = 6 for tetrahedra and pyramids, P >= 9); none in
+// FP32 elsewhere (tetrahedra at P = 7: 290 -> 260 us).  Affine elements, whose folded point loop
+// needs more registers: both in FP64 (prisms at P = 8: 319, 272 and 193 us with none, the third and
+// both), the third in FP32.
+template <int SHAPE, int P, class T, bool DEF>
+constexpr int col_lds_planes() {
+  if (!DEF) return sizeof(T) == 8 ? 2 : 1;
+  return sizeof(T) == 8 || P >= 9 || (P == 6 && SHAPE != kPrism) ? 1 : 0;
+}
+// Whether the first point's factors are requested before sweep A and stay in flight through A and
+// B.  At P = 2 the sweeps are too short to pay for the registers (FP64 pyramids 36.4 -> 29.4 us
+// without); affine elements request point weights only.
+template <int SHAPE, int P, class T, bool DEF>
+constexpr bool col_early() {
+  return DEF && P > 2;
+}
+
 // OPM = 1: the backward transform only (u = B c at the points, into y[nelmt][Q^3]): the value
 // halves of A and B, then C without the pointwise step; helm and lambda are not used.
 // OPM = 2: the inner product with the basis only (y = B^T W u for u = x[nelmt][Q^3], W = w |J|
@@ -160,7 +191,8 @@ struct ColUnit {
 // wavefronts past the last group only take part in the barriers); `lds` holds NSUB * LDS
 // values.  Every thread of the block must call it (it synchronises).
 // pen: the direction-1 factor and its derivative in [point][mode] layout (B then B').
-template <int SHAPE, int P, class T, bool DEF, int E_ = 0, int NSUB = 1, int OPM = 0>
+template <int SHAPE, int P, class T, bool DEF, int E_ = 0, int NSUB = 1, int OPM = 0, int LV = col_lds_planes<SHAPE, P, T, DEF>(),
+          bool EARLY = col_early<SHAPE, P, T, DEF>()>
 __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __restrict__ pen, const T* __restrict__ x,
                                                T* __restrict__ y, const T* __restrict__ helm, T lambda, int64_t nelmt,
                                                int64_t base0, T* __restrict__ lds0, const T* __restrict__ x1 = nullptr,
@@ -174,11 +206,12 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
   constexpr int PQ2 = P * Q2;
   constexpr bool TET = SHAPE == kTet, PYR = SHAPE == kPyr;
   constexpr bool VTX = TET || PYR;   // a vertex mode (0,0,1) handled point by point
+  using F = EoDims<P>;
+  constexpr int H = F::H, NE = F::NE, NO = F::NO, ROW = F::ROW;
+  constexpr bool FOLD = !DEF, C2L = LV >= 1, C1L = LV >= 2;
 
   static_assert(E * Q <= 64, "a slice wavefront holds E elements x Q lanes");
   static_assert(!PYR || E * (2 * P - 1) <= 128, "a pyramid slice takes at most two passes of its wavefront");
-  static_assert(TET || (col_b_terms(SHAPE, P, 0) == P && col_b_off(SHAPE, P, 1) == P * Q),
-                "prism and pyramid B rows: P terms per point, planes P Q values apart");
   const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int sub = wave0 / D::NW;                       // group of this wavefront
   const bool in = sub < NSUB;
@@ -204,6 +237,32 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
     lds[e2 * SLAB + (f - e2 * M)] = x[base * M + f];
   }
   __syncthreads();
+
+  // The factors of the point pair (h, Q-1-h), or of the middle point alone, as buffer loads: a byte
+  // offset per lane for the whole point loop and the (component, plane) offset in a scalar register;
+  // lanes past the last element read past the descriptor's size and get zeros.  The first pair's are
+  // requested here and stay in flight through sweeps A and B (barriers do not wait for loads).
+  // Affine elements request the points' weights instead.
+  constexpr bool HELM = !BWD && !NOFWD;
+  const bool pencils = in && wave < D::NWP;
+  const __amdgpu_buffer_rsrc_t grs = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<T*>(HELM && DEF ? helm + base * (7 * NQ) : tb.wq), short(0),
+      (HELM && DEF ? ne * 7 * NQ : NQ) * int(sizeof(T)), 0x00020000);
+  const int gvo = (HELM && DEF ? el * 7 * NQ + s : s) * int(sizeof(T));
+  T gn[!HELM ? 1 : (DEF ? 7 : 1) * (FOLD ? 2 : 1)];
+  auto request = [&](int h, bool one) {
+#pragma unroll
+    for (int c = 0; c < (DEF ? 7 : 1); ++c) gn[c] = buf_load<T>(grs, gvo, ((DEF ? c * NQ : 0) + h * Q2) * int(sizeof(T)));
+    if constexpr (FOLD) {
+      if (one) return;
+#pragma unroll
+      for (int c = 0; c < (DEF ? 7 : 1); ++c)
+        gn[(DEF ? 7 : 1) + c] = buf_load<T>(grs, gvo, ((DEF ? c * NQ : 0) + (Q - 1 - h) * Q2) * int(sizeof(T)));
+    }
+  };
+  if constexpr (HELM && DEF && EARLY) {
+    if (pencils) request(0, !FOLD);
+  }
 
   // ---- A: r -> k, one slice (tet: s = p+q, prism: p, pyramid: max(p,q)) per wavefront
   T c001 = T(0);
@@ -362,7 +421,7 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
     T* Ls = lds + (e2 < E ? e2 : 0) * SLAB;
     int pw = -1;
     // the tet's factor psi^b_pq depends on p: one body per plane; the prism's and the pyramid's
-    // psi^a_q does not: one body, p at run time (the rows of every plane are alike)
+    // psi^a_q does not: one body, p at run time
     auto stageB = [&](auto ic, const int p) {
       constexpr int pc = decltype(ic)::value, nq = MO::nq(pc);
       constexpr bool X = TET && pc == 1;   // pair (0,1) enters the p = 1 plane
@@ -377,31 +436,63 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
           av[nq] = Ls[MO::pair(0, 1) * Q + k];
           if constexpr (!BWD) bv[nq] = Ls[NP * Q + MO::pair(0, 1) * Q + k];
         }
-        // one row of terms per point j (transposed table), the pair (0,1) term last for X
-        constexpr int nt = col_b_terms(SHAPE, P, pc);
-        const int off = TET ? col_b_off(SHAPE, P, pc) : p * (P * Q);
-        static_assert(nt == nq + (X ? 1 : 0), "B terms");
-#pragma unroll
-        for (int j = 0; j < Q; ++j) {
-          const T dep = j > 0 ? b0[j - 1] : av[0];
-          const const_ptr<T> f = fresh_table_after(tb.T2t, dep) + (off + j * nt);
-          const const_ptr<T> df = fresh_table_after(tb.dT2t, dep) + (off + j * nt);
-          T v0 = T(0), v1 = T(0), v2 = T(0);
-#pragma unroll
-          for (int q = 0; q < nt; ++q) {
-            v0 += f[q] * av[q];
+        if constexpr (TET) {
+          // one row of terms per point j (transposed table), the pair (0,1) term last for X
+          constexpr int nt = col_b_terms(SHAPE, P, pc);
+          constexpr int off = col_b_off(SHAPE, P, pc);
+          static_assert(nt == nq + (X ? 1 : 0), "B terms");
+  #pragma unroll
+          for (int j = 0; j < Q; ++j) {
+            const T dep = j > 0 ? b0[j - 1] : av[0];
+            const const_ptr<T> f = fresh_table_after(tb.T2t, dep) + (off + j * nt);
+            const const_ptr<T> df = fresh_table_after(tb.dT2t, dep) + (off + j * nt);
+            T v0 = T(0), v1 = T(0), v2 = T(0);
+  #pragma unroll
+            for (int q = 0; q < nt; ++q) {
+              v0 += f[q] * av[q];
+              if constexpr (!BWD) {
+                v1 += df[q] * av[q];
+                v2 += f[q] * bv[q];
+              }
+            }
+            b0[j] = v0;
+            b1[j] = v1;
+            b2[j] = v2;
+            row_fence<1>(&b0[j]);
             if constexpr (!BWD) {
-              v1 += df[q] * av[q];
-              v2 += f[q] * bv[q];
+              row_fence<1>(&b1[j]);
+              row_fence<1>(&b2[j]);
             }
           }
-          b0[j] = v0;
-          b1[j] = v1;
-          b2[j] = v2;
-          row_fence<1>(&b0[j]);
-          if constexpr (!BWD) {
-            row_fence<1>(&b1[j]);
-            row_fence<1>(&b2[j]);
+        } else {
+          // psi^a_q on Gauss-Lobatto points: folded over the point pairs (j, Q-1-j)
+          T ea[NE], oa[NO], eb[NE], ob[NO];
+          eo_fold<P>(av, ea, oa);
+          if constexpr (!BWD) eo_fold<P>(bv, eb, ob);
+#pragma unroll
+          for (int h = 0; h < H; ++h) {
+            const T dep = h > 0 ? b0[h - 1] : av[0];
+            const HexTabEO<P, T> tk{fresh_table_after(tb.eo, dep) + h * ROW};
+            const bool mid = F::MID && h == H - 1;
+            T S0, A0, SD = T(0), AD = T(0), S2 = T(0), A2 = T(0);
+            eo_val(tk, ea, oa, S0, A0, mid);
+            if constexpr (!BWD) {
+              eo_der(tk, ea, oa, SD, AD, mid);
+              eo_val(tk, eb, ob, S2, A2, mid);
+            }
+            b0[h] = S0 + A0;
+            b1[h] = SD + AD;
+            b2[h] = S2 + A2;
+            if (!mid) {
+              b0[Q - 1 - h] = S0 - A0;
+              b1[Q - 1 - h] = SD - AD;
+              b2[Q - 1 - h] = S2 - A2;
+            }
+            row_fence<1>(&b0[h]);
+            if constexpr (!BWD) {
+              row_fence<1>(&b1[h]);
+              row_fence<1>(&b2[h]);
+            }
           }
         }
         pw = p;
@@ -553,146 +644,208 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
     __syncthreads();
   }
 
-  // ---- C, pointwise, C^T fused over the (j,k) pencils, streamed over i (the wavefronts without
-  // pencils go straight to the barrier)
+  // ---- C, pointwise, C^T fused over the (j,k) pencils, streamed over the points i or the point pairs
+  // (i, Q-1-i) (the wavefronts without pencils go straight to the barrier)
   if constexpr (!NOFWD) {
-    T C0[P], C1[P], C2[P];
-    T t0[P], t1[P], t2[P];
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      C0[p] = act ? L[p * Q2 + s] : T(0);
-      C1[p] = act ? L[PQ2 + p * Q2 + s] : T(0);
-      C2[p] = act ? L[2 * PQ2 + p * Q2 + s] : T(0);
-      t0[p] = t1[p] = t2[p] = T(0);
-    }
-    // chain-rule factors of the pencil: d eta / d xi (eq. (23))
-    const T e2v = tb.z[1][act ? jj : 0], e3v = tb.z[2][act ? kk : 0];
-    // c01 = c02 = c1k (1 + eta1) for the tet, c02 = c1k (1 + eta1) for the prism and the pyramid
-    T c00, c1k, c11, c12;
-    if (TET) {
-      const T r3 = T(1) / (T(1) - e3v);
-      const T ra = r3 / (T(1) - e2v);
-      c00 = T(4) * ra;
-      c1k = T(2) * ra;
-      c11 = T(2) * r3;
-      c12 = (T(1) + e2v) * r3;
-    } else if (PYR) {
-      const T r3 = T(1) / (T(1) - e3v);
-      c00 = T(2) * r3;
-      c1k = r3;
-      c11 = T(2) * r3;
-      c12 = (T(1) + e2v) * r3;
-    } else {
-      const T r3 = T(1) / (T(1) - e3v);
-      c00 = T(2) * r3;
-      c1k = r3;
-      c11 = T(1);
-      c12 = T(0);
-    }
-    T vc = T(0), vd = T(0);   // vertex mode (0,0,1): value and eta3-derivative factor at k
-    if (VTX) {
-      vc = tb.T3[1 * Q + (act ? kk : 0)];
-      vd = tb.dT3[1 * Q + (act ? kk : 0)];
-    }
-    const T uv = c001 * vc, dv = c001 * vd;
+    // chain-rule factors of the pencil (eq. (23)): d eta1 / d xi1 = 2 k1 and, with z1 = 1 + eta1,
+    // d eta1 / d xi3 = k1 z1 (tet: / d xi2 too); d eta2 / d xi2 = 2 k2 and d eta2 / d xi3 = k2 e2
+    // (tet and pyramid; 1 and 0 for the prism)
+    const T e2 = T(1) + tb.z[1][act ? jj : 0], r3 = T(1) / (T(1) - tb.z[2][act ? kk : 0]);
+    const T k1 = TET ? T(2) * r3 / (T(2) - e2) : r3, k2 = r3;
+    const int vk = 1 * Q + (act ? kk : 0);   // the vertex mode (0,0,1) in T3, dT3
+    const T uv = VTX ? c001 * tb.T3[vk] : T(0), dv = VTX ? c001 * tb.dT3[vk] : T(0);
     T vm = T(0), v3 = T(0);
-    if (in && wave < D::NWP) {
-      // The point loop is unrolled where the registers allow (FP64: tetrahedra to P = 9, affine
-      // prisms, prisms with per-point factors to P = 7).  The factors of point plane i+1 (per
-      // point) or its weight (affine) are requested once plane i's are consumed, so the rest of
-      // iteration i covers their latency (rolled, the last plane requests itself again, a cache
-      // hit).  Lanes past the batch end read element 0's (in bounds, finite, never stored).
-      constexpr bool UNR = sizeof(T) == 4 || (TET ? P <= 9 : (!DEF || P <= 7));
-      const T* g = helm + (valid ? int64_t(base + el) : 0) * (DEF ? 7 * NQ : 7);
-      T gn[DEF ? 7 : 1], ga[DEF ? 1 : 7];
-      if constexpr (DEF) {
-#pragma unroll
-        for (int c = 0; c < 7; ++c) gn[c] = g[c * NQ + s];
-      } else {
-#pragma unroll
-        for (int c = 0; c < 7; ++c) ga[c] = g[c];
-        gn[0] = tb.wq[s];
+    // one point: from the values and eta derivatives the weighted mass term m, the fluxes h1, h2 of
+    // the first two eta directions and y3 of the third
+    auto point = [&](T u, T d1, T d2, T d3, const T* G, T z1, T& m, T& h1, T& h2, T& y3) {
+      if (VTX) {
+        u += uv;
+        d3 += dv;
       }
-#pragma unroll(UNR ? Q : 1)
-      for (int i = 0; i < Q; ++i) {
-        const HexTabC<P, T> tk{fresh_table(pen)};
-        T u = T(0), d1 = T(0), d2 = T(0), d3 = T(0);
+      const T td = k1 * d1, x1 = T(2) * td;
+      T x2, x3;
+      if (TET) {
+        const T w = k2 * d2, c = z1 * td;
+        x2 = c + T(2) * w;
+        x3 = c + e2 * w + d3;
+      } else if (PYR) {
+        const T w = k1 * d2;
+        x2 = T(2) * w;
+        x3 = z1 * td + e2 * w + d3;
+      } else {
+        x2 = d2;
+        x3 = z1 * td + d3;
+      }
+      const T y1 = G[0] * x1 + G[1] * x2 + G[2] * x3;
+      const T y2 = G[1] * x1 + G[3] * x2 + G[4] * x3;
+      y3 = G[2] * x1 + G[4] * x2 + G[5] * x3;
+      m = lambda * G[6] * u;
+      h1 = k1 * (T(2) * y1 + z1 * (TET ? y2 + y3 : y3));
+      h2 = TET ? k2 * (T(2) * y2 + e2 * y3) : (PYR ? k1 * (T(2) * y2 + e2 * y3) : y2);
+      if (VTX) {
+        vm += m;
+        v3 += y3;
+      }
+      asm volatile("" : "+v"(m), "+v"(h1), "+v"(h2), "+v"(y3));
+    };
+    // factors of the affine element (7, read once per pencil; gn holds the point weights)
+    T ga[DEF ? 1 : 7];
+    if constexpr (!DEF) {
+      const T* g = helm + (valid ? int64_t(base + el) : 0) * 7;
 #pragma unroll
-        for (int p = 0; p < P; ++p) {
-          const T f = tk.B(i, p), df = tk.D(i, p);
-          u += f * C0[p];
-          d1 += df * C0[p];
-          d2 += f * C1[p];
-          d3 += f * C2[p];
-        }
-        if (VTX) {
-          u += uv;
-          d3 += dv;
-        }
-        T G[7];
-        if constexpr (DEF) {
+      for (int c = 0; c < 7; ++c) ga[c] = g[c];
+    }
+    auto factors = [&](int q, T* G) {
 #pragma unroll
-          for (int c = 0; c < 7; ++c) G[c] = gn[c];
-        } else {
+      for (int c = 0; c < 7; ++c) G[c] = DEF ? gn[DEF ? 7 * q + c : 0] : ga[DEF ? 0 : c] * gn[DEF ? 0 : q];
+    };
+    // a plane of this pencil that stays in LDS; the lane's offset passes an empty asm, so that the
+    // addresses are formed here and not hoisted out of the loop into long-lived registers
+    auto plane = [&](int which, T* c) {
+      int so = (act ? el : 0) * SLAB + which * PQ2 + s;
+      asm volatile("" : "+v"(so));
 #pragma unroll
-          for (int c = 0; c < 7; ++c) G[c] = ga[c] * gn[0];
+      for (int p = 0; p < P; ++p) c[p] = lds[p * Q2 + so];
+    };
+    T t0[P], t1[P], t2[P];
+    if constexpr (FOLD) {
+      T C0e[NE], C0o[NO], C1e[NE], C1o[NO], C2e[NE], C2o[NO];
+      {
+        T tmp[P];
+        plane(0, tmp);
+        eo_fold<P>(tmp, C0e, C0o);
+        if constexpr (!C1L) {
+          plane(1, tmp);
+          eo_fold<P>(tmp, C1e, C1o);
         }
-        const T c1 = c1k * (T(1) + tb.z[0][i]);
-        T x1, x2, x3;
-        if (TET) {
-          x1 = c00 * d1;
-          x2 = c1 * d1 + c11 * d2;
-          x3 = c1 * d1 + c12 * d2 + d3;
-        } else if (PYR) {
-          x1 = c00 * d1;
-          x2 = c11 * d2;
-          x3 = c1 * d1 + c12 * d2 + d3;
-        } else {
-          x1 = c00 * d1;
-          x2 = d2;
-          x3 = c1 * d1 + d3;
+        if constexpr (!C2L) {
+          plane(2, tmp);
+          eo_fold<P>(tmp, C2e, C2o);
         }
-        T y1 = G[0] * x1 + G[1] * x2 + G[2] * x3;
-        T y2 = G[1] * x1 + G[3] * x2 + G[4] * x3;
-        T y3 = G[2] * x1 + G[4] * x2 + G[5] * x3;
-        T m = lambda * G[6] * u;
-        if (!UNR || i + 1 < Q) {
-          // these factors are consumed: the next plane's into the same registers (unrolled, its
-          // address is opaque from here on, so the loads are issued here and not earlier)
-          asm volatile("" : "+v"(y1), "+v"(y2), "+v"(y3), "+v"(m));
-          __builtin_amdgcn_sched_barrier(0);
-          const int nn = (i + 1 < Q ? i + 1 : i) * Q2 + s;
-          const T* gp = DEF ? g + nn : tb.wq + nn;
-          if constexpr (UNR) asm volatile("" : "+v"(gp));
-          if constexpr (DEF) {
+      }
+      T E0[NE], O0[NO], E1[NE], O1[NO], E2[NE], O2[NO];
 #pragma unroll
-            for (int c = 0; c < 7; ++c) gn[c] = gp[c * NQ];
+      for (int k = 0; k < NE; ++k) E0[k] = E1[k] = E2[k] = T(0);
+#pragma unroll
+      for (int k = 0; k < NO; ++k) O0[k] = O1[k] = O2[k] = T(0);
+      if (pencils) {
+        if constexpr (!DEF || !EARLY) request(0, false);
+        // one pair (h, Q-1-h), or the middle point alone (MP): forward, pointwise, the request of
+        // the next pair's factors into the registers just consumed, backward
+        auto pair = [&](auto mpc, int h, bool more) {
+          constexpr bool MP = decltype(mpc)::value;
+          constexpr int NPT = MP ? 1 : 2;
+          const HexTabEO<P, T> tk{fresh_table(tb.eo) + h * ROW};
+          T u[2], d1[2], d2[2], d3[2], S, A;
+          eo_val(tk, C0e, C0o, S, A, MP);
+          u[0] = S + A;
+          u[1] = S - A;
+          eo_der(tk, C0e, C0o, S, A, MP);
+          d1[0] = S + A;
+          d1[1] = S - A;
+          if constexpr (C1L) {
+            T tmp[P], ev[NE], od[NO];
+            plane(1, tmp);
+            eo_fold<P>(tmp, ev, od);
+            eo_val(tk, ev, od, S, A, MP);
           } else {
-            gn[0] = *gp;
+            eo_val(tk, C1e, C1o, S, A, MP);
           }
-        }
-        T h1, h2;
-        if (TET) {
-          h1 = c00 * y1 + c1 * (y2 + y3);
-          h2 = c11 * y2 + c12 * y3;
-          vm += m;
-          v3 += y3;
-        } else if (PYR) {
-          h1 = c00 * y1 + c1 * y3;
-          h2 = c11 * y2 + c12 * y3;
-          vm += m;
-          v3 += y3;
-        } else {
-          h1 = c00 * y1 + c1 * y3;
-          h2 = y2;
-        }
+          d2[0] = S + A;
+          d2[1] = S - A;
+          if constexpr (C1L) __builtin_amdgcn_sched_barrier(0);   // one transient pencil at a time
+          if constexpr (C2L) {
+            T tmp[P], ev[NE], od[NO];
+            plane(2, tmp);
+            eo_fold<P>(tmp, ev, od);
+            eo_val(tk, ev, od, S, A, MP);
+          } else {
+            eo_val(tk, C2e, C2o, S, A, MP);
+          }
+          d3[0] = S + A;
+          d3[1] = S - A;
+          T m[2], h1[2], h2[2], y3[2];
 #pragma unroll
-        for (int p = 0; p < P; ++p) {
-          const T f = tk.B(i, p), df = tk.D(i, p);
-          t0[p] += f * m;
-          t0[p] += df * h1;
-          t1[p] += f * h2;
-          t2[p] += f * y3;
+          for (int q = 0; q < NPT; ++q) {
+            T G[7];
+            factors(q, G);
+            point(u[q], d1[q], d2[q], d3[q], G, T(1) + tb.z[0][q == 0 ? h : Q - 1 - h], m[q], h1[q], h2[q], y3[q]);
+          }
+          if (more) {
+            __builtin_amdgcn_sched_barrier(0);
+            request(h + 1, F::MID && h + 1 == H - 1);
+          }
+          if constexpr (MP) {
+            eo_tval(tk, m[0], T(0), E0, O0, true);
+            eo_tder(tk, h1[0], T(0), E0, O0, true);
+            eo_tval(tk, h2[0], T(0), E1, O1, true);
+            eo_tval(tk, y3[0], T(0), E2, O2, true);
+          } else {
+            eo_tval(tk, m[0] + m[1], m[0] - m[1], E0, O0);
+            eo_tder(tk, h1[0] + h1[1], h1[0] - h1[1], E0, O0);
+            eo_tval(tk, h2[0] + h2[1], h2[0] - h2[1], E1, O1);
+            eo_tval(tk, y3[0] + y3[1], y3[0] - y3[1], E2, O2);
+          }
+        };
+#pragma unroll(sizeof(T) == 4 ? Q / 2 : 1)
+        for (int h = 0; h < Q / 2; ++h) pair(std::false_type{}, h, h + 1 < H);
+        if constexpr (F::MID) pair(std::true_type{}, H - 1, false);
+      }
+      eo_unfold<P>(E0, O0, t0);
+      eo_unfold<P>(E1, O1, t1);
+      eo_unfold<P>(E2, O2, t2);
+    } else {
+      T C0[P], C1[C1L ? 1 : P], C2[C2L ? 1 : P];
+      plane(0, C0);
+      if constexpr (!C1L) plane(1, C1);
+      if constexpr (!C2L) plane(2, C2);
+#pragma unroll
+      for (int p = 0; p < P; ++p) t0[p] = t1[p] = t2[p] = T(0);
+      if (pencils) {
+        if constexpr (!DEF || !EARLY) request(0, true);
+        constexpr bool UNR = sizeof(T) == 4 || (TET ? P <= 9 : P <= 7);
+#pragma unroll(UNR ? Q : 1)
+        for (int i = 0; i < Q; ++i) {
+          const HexTabC<P, T> tk{fresh_table(pen)};
+          T u = T(0), d1 = T(0), d2 = T(0), d3 = T(0);
+#pragma unroll
+          for (int p = 0; p < P; ++p) {
+            u += tk.B(i, p) * C0[p];
+            d1 += tk.D(i, p) * C0[p];
+          }
+          if constexpr (C1L) {
+            T c[P];
+            plane(1, c);
+#pragma unroll
+            for (int p = 0; p < P; ++p) d2 += tk.B(i, p) * c[p];
+          } else {
+#pragma unroll
+            for (int p = 0; p < P; ++p) d2 += tk.B(i, p) * C1[p];
+          }
+          if constexpr (C2L) {
+            T c[P];
+            plane(2, c);
+#pragma unroll
+            for (int p = 0; p < P; ++p) d3 += tk.B(i, p) * c[p];
+          } else {
+#pragma unroll
+            for (int p = 0; p < P; ++p) d3 += tk.B(i, p) * C2[p];
+          }
+          T G[7], m, h1, h2, y3;
+          factors(0, G);
+          point(u, d1, d2, d3, G, T(1) + tb.z[0][i], m, h1, h2, y3);
+          if (i + 1 < Q) {
+            __builtin_amdgcn_sched_barrier(0);
+            request(i + 1, true);
+          }
+#pragma unroll
+          for (int p = 0; p < P; ++p) {
+            const T f = tk.B(i, p), df = tk.D(i, p);
+            t0[p] += f * m;
+            t0[p] += df * h1;
+            t1[p] += f * h2;
+            t2[p] += f * y3;
+          }
         }
       }
     }
@@ -704,7 +857,7 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
         L[PQ2 + p * Q2 + s] = t1[p];
         L[2 * PQ2 + p * Q2 + s] = t2[p];
       }
-      if (VTX) L[MAIN + s] = vc * vm + vd * v3;
+      if (VTX) L[MAIN + s] = tb.T3[vk] * vm + tb.dT3[vk] * v3;
     }
     __syncthreads();
   }
@@ -734,27 +887,58 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
 #pragma unroll
           for (int j = 0; j < Q; ++j) sx += Ls[MAIN + j * Q + k];
         }
-        // outer loop over the points j, one row of terms per point (transposed table): only that
-        // row is live in SGPRs; the pair (0,1) term last for X
-        constexpr int nt = col_b_terms(SHAPE, P, pc);
-        const int off = TET ? col_b_off(SHAPE, P, pc) : p * (P * Q);
+        if constexpr (TET) {
+          // outer loop over the points j, one row of terms per point (transposed table): only that
+          // row is live in SGPRs; the pair (0,1) term last for X
+          constexpr int nt = col_b_terms(SHAPE, P, pc);
+          constexpr int off = col_b_off(SHAPE, P, pc);
+  #pragma unroll
+          for (int q = 0; q < nt; ++q) s0[q] = s1[q] = T(0);
+  #pragma unroll
+          for (int j = 0; j < Q; ++j) {
+            const T dep = j > 0 ? (IPR ? s0[nt - 1] : s1[nt - 1]) : tv0[0];
+            const const_ptr<T> f = fresh_table_after(tb.T2t, dep) + (off + j * nt);
+            const const_ptr<T> df = fresh_table_after(tb.dT2t, dep) + (off + j * nt);
+  #pragma unroll
+            for (int q = 0; q < nt; ++q) {
+              s0[q] += f[q] * tv0[j];
+              if constexpr (!IPR) {
+                s0[q] += df[q] * tv1[j];
+                s1[q] += f[q] * tv2[j];
+              }
+            }
+            row_fence<nt>(s0);
+            if constexpr (!IPR) row_fence<nt>(s1);
+          }
+        } else {
+          T E0[NE], O0[NO], E1[NE], O1[NO];
 #pragma unroll
-        for (int q = 0; q < nt; ++q) s0[q] = s1[q] = T(0);
+          for (int k2 = 0; k2 < NE; ++k2) E0[k2] = E1[k2] = T(0);
 #pragma unroll
-        for (int j = 0; j < Q; ++j) {
-          const T dep = j > 0 ? (IPR ? s0[nt - 1] : s1[nt - 1]) : tv0[0];
-          const const_ptr<T> f = fresh_table_after(tb.T2t, dep) + (off + j * nt);
-          const const_ptr<T> df = fresh_table_after(tb.dT2t, dep) + (off + j * nt);
+          for (int k2 = 0; k2 < NO; ++k2) O0[k2] = O1[k2] = T(0);
 #pragma unroll
-          for (int q = 0; q < nt; ++q) {
-            s0[q] += f[q] * tv0[j];
+          for (int h = 0; h < H; ++h) {
+            const T dep = h > 0 ? (IPR ? O0[NO - 1] : O1[NO - 1]) : tv0[0];
+            const HexTabEO<P, T> tk{fresh_table_after(tb.eo, dep) + h * ROW};
+            const bool mid = F::MID && h == H - 1;
+            T sv, dv;
+            eo_pair<P>(tv0, h, mid, sv, dv);
+            eo_tval(tk, sv, dv, E0, O0, mid);
             if constexpr (!IPR) {
-              s0[q] += df[q] * tv1[j];
-              s1[q] += f[q] * tv2[j];
+              eo_pair<P>(tv1, h, mid, sv, dv);
+              eo_tder(tk, sv, dv, E0, O0, mid);
+              eo_pair<P>(tv2, h, mid, sv, dv);
+              eo_tval(tk, sv, dv, E1, O1, mid);
+            }
+            row_fence<NE>(E0);
+            row_fence<NO>(O0);
+            if constexpr (!IPR) {
+              row_fence<NE>(E1);
+              row_fence<NO>(O1);
             }
           }
-          row_fence<nt>(s0);
-          if constexpr (!IPR) row_fence<nt>(s1);
+          eo_unfold<P>(E0, O0, s0);
+          if constexpr (!IPR) eo_unfold<P>(E1, O1, s1);
         }
         pw = p;
       }

@@ -68,9 +68,11 @@ struct DevTab {
   const T* xi;
   const int32_t* pair;
   const int32_t* mode_pqr;
-  // collapsed shapes: the factors of the forward sweeps A (direction 3) and B (direction 2) of the
-  // register-pencil kernel, transposed to one row of terms per output point and slice (layout of
-  // col_a_off / col_b_off), and their derivatives
+  // the direction-1 factor folded by even-odd symmetry (eo_fold.h), [ceil(Q/2)][2P]
+  const T* eo;
+  // collapsed shapes: the factors of the forward sweeps A (direction 3) and, for the tetrahedron, B
+  // (direction 2) of the register-pencil kernel, transposed to one row of terms per output point
+  // and slice (layout of col_a_off / col_b_off), and their derivatives
   const T* T3t;
   const T* dT3t;
   const T* T2t;
