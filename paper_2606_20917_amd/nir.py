@@ -141,6 +141,8 @@ def _ptr(x):
 
 
 _TORCH_DT = {F64: "float64", F32: "float32"}
+_dtypes = {}     # F64, F32, "int32" -> torch.dtype, filled at the first match by name
+_modes = {}      # (shape, P) -> mode count of valid shapes and orders
 
 
 def _need(x, name, count, dt, device=False):
@@ -150,10 +152,12 @@ def _need(x, name, count, dt, device=False):
     integer addresses pass through (the C side rejects NULL where it needs a pointer)."""
     if x is None or isinstance(x, int):
         return
-    want = _TORCH_DT.get(dt, dt)
-    got = str(x.dtype).replace("torch.", "")
-    if got != want:
-        raise NirError(1, f"{name}: element type {got}, the call needs {want}")
+    if x.dtype is not _dtypes.get(dt):
+        want = _TORCH_DT.get(dt, dt)
+        got = str(x.dtype).replace("torch.", "")
+        if got != want:
+            raise NirError(1, f"{name}: element type {got}, the call needs {want}")
+        _dtypes[dt] = x.dtype
     if x.numel() < count:
         raise NirError(1, f"{name}: {x.numel()} elements, the call needs at least {count}")
     if device:
@@ -162,14 +166,20 @@ def _need(x, name, count, dt, device=False):
 
 def _dims(b):
     """(nelmt, M, Q^3, geometry points per element) of a batch; M = 0 for an invalid shape/order."""
-    M = max(0, int(lib().nir_nmodes(b.shape, b.nmodes)))
+    key = b.shape, b.nmodes
+    M = _modes.get(key)
+    if M is None:
+        M = max(0, int(lib().nir_nmodes(*key)))
+        if M and key[1] <= 16:
+            _modes[key] = M
     nq = b.nquad ** 3
     return b.nelmt, M, nq, (nq if b.deformed else 1)
 
 
-def _need_geom(b, g, dxi=False, jac=False, helm=False, dt=None):
-    """Check the tensors a nir_geom was built from (nir.geom keeps them) against the batch."""
-    ne, _, _, ng = _dims(b)
+def _need_geom(b, g, dxi=False, jac=False, helm=False, dt=None, dims=None):
+    """Check the tensors a nir_geom was built from (nir.geom keeps them) against the batch (whose
+    _dims the caller may pass)."""
+    ne, _, _, ng = _dims(b) if dims is None else dims
     dt = b.dtype if dt is None else dt
     t = getattr(g, "_tensors", (None, None, None))
     if dxi:
@@ -180,11 +190,24 @@ def _need_geom(b, g, dxi=False, jac=False, helm=False, dt=None):
         _need(t[2], "geom.helm", ne * 7 * ng, dt, device=True)
 
 
+_current = None   # (device index, its current stream's address) getters of an initialised torch
+
+
 def _stream(stream):
+    """Address of the stream to enqueue on: the one given, or torch's current stream of the current
+    device, asked for at every call (through torch's own getters once torch is initialised: a
+    Stream object for each call costs as much as the kernel launch, 1.7 us)."""
+    global _current
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
+    if _current is not None:
+        return _current[1](_current[0]())
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    s = torch.cuda.current_stream().cuda_stream   # initialises torch
+    get = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if None not in get:
+        _current = get[1], get[0]
+    return s
 
 
 def batch(shape, P, nelmt, dtype=F64, deformed=1, math=MATH_NATIVE, Q=None):
@@ -302,47 +325,52 @@ def nir_bwd_trans(b, basis, coef, phys, stream=None):
 
 
 def nir_phys_deriv(b, basis, g, phys, d0, d1, d2, stream=None):
-    ne, M, nq, _ = _dims(b)
+    dims = _dims(b)
+    ne, M, nq, _ = dims
     for name, t in (("phys", phys), ("d0", d0), ("d1", d1), ("d2", d2)):
         _need(t, name, ne * nq, b.dtype)
-    _need_geom(b, g, dxi=True)
+    _need_geom(b, g, dxi=True, dims=dims)
     _check(lib().nir_phys_deriv(ctypes.byref(b), _basis(basis), ctypes.byref(g), _ptr(phys), _ptr(d0), _ptr(d1),
                                 _ptr(d2), _stream(stream)))
 
 
 def nir_iprod_wrt_base(b, basis, g, phys, coef, stream=None):
-    ne, M, nq, _ = _dims(b)
+    dims = _dims(b)
+    ne, M, nq, _ = dims
     _need(phys, "phys", ne * nq, b.dtype)
     _need(coef, "coef", ne * M, b.dtype)
-    _need_geom(b, g, jac=True)
+    _need_geom(b, g, jac=True, dims=dims)
     _check(lib().nir_iprod_wrt_base(ctypes.byref(b), _basis(basis), ctypes.byref(g), _ptr(phys), _ptr(coef),
                                     _stream(stream)))
 
 
 def nir_iprod_wrt_deriv_base(b, basis, g, f0, f1, f2, coef, stream=None):
-    ne, M, nq, _ = _dims(b)
+    dims = _dims(b)
+    ne, M, nq, _ = dims
     for name, t in (("f0", f0), ("f1", f1), ("f2", f2)):
         _need(t, name, ne * nq, b.dtype)
     _need(coef, "coef", ne * M, b.dtype)
-    _need_geom(b, g, dxi=True, jac=True)
+    _need_geom(b, g, dxi=True, jac=True, dims=dims)
     _check(lib().nir_iprod_wrt_deriv_base(ctypes.byref(b), _basis(basis), ctypes.byref(g), _ptr(f0), _ptr(f1),
                                           _ptr(f2), _ptr(coef), _stream(stream)))
 
 
 def nir_helmholtz_apply(b, basis, g, lam, coef_in, coef_out, stream=None):
-    ne, M, _, _ = _dims(b)
+    dims = _dims(b)
+    ne, M, _, _ = dims
     _need(coef_in, "coef_in", ne * M, b.dtype)
     _need(coef_out, "coef_out", ne * M, b.dtype)
-    _need_geom(b, g, helm=True)
+    _need_geom(b, g, helm=True, dims=dims)
     _check(lib().nir_helmholtz_apply(ctypes.byref(b), _basis(basis), ctypes.byref(g), lam, _ptr(coef_in),
                                      _ptr(coef_out), _stream(stream)))
 
 
 def nir_helmholtz_apply_fields(b, basis, g, lam, nfields, coef_in, coef_out, stream=None):
-    ne, M, _, _ = _dims(b)
+    dims = _dims(b)
+    ne, M, _, _ = dims
     _need(coef_in, "coef_in", ne * max(nfields, 0) * M, b.dtype)
     _need(coef_out, "coef_out", ne * max(nfields, 0) * M, b.dtype)
-    _need_geom(b, g, helm=True)
+    _need_geom(b, g, helm=True, dims=dims)
     _check(lib().nir_helmholtz_apply_fields(ctypes.byref(b), _basis(basis), ctypes.byref(g), lam, nfields,
                                             _ptr(coef_in), _ptr(coef_out), _stream(stream)))
 
@@ -357,10 +385,11 @@ def nir_helmholtz_apply_trilinear(b, basis, verts, lam, coef_in, coef_out, strea
 
 
 def nir_helmholtz_apply_nodal(b, basis, g, lam, u_in, u_out, stream=None):
-    ne, _, nq, _ = _dims(b)
+    dims = _dims(b)
+    ne, _, nq, _ = dims
     _need(u_in, "u_in", ne * nq, b.dtype)
     _need(u_out, "u_out", ne * nq, b.dtype)
-    _need_geom(b, g, helm=True)
+    _need_geom(b, g, helm=True, dims=dims)
     _check(lib().nir_helmholtz_apply_nodal(ctypes.byref(b), _basis(basis), ctypes.byref(g), lam, _ptr(u_in),
                                            _ptr(u_out), _stream(stream)))
 
