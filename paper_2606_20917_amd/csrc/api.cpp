@@ -124,6 +124,7 @@ bool helm_gathers(const nir_basis* basis, int dtype) {
 nir_status launch_helm_auto(const nir_basis* basis, int dtype, int deformed, const OpArgs& a, hipStream_t s) {
   int v = resolve_variant(basis->shape, basis->P, dtype);
   if (v == NIR_VARIANT_DENSE) {
+    if (basis->shape == kTet && !deformed && basis->grad64) return launch_helm_grad(basis, dtype, a, s);
     if (basis->shape != kHex && !deformed && basis->dense64) return launch_helm_dense(basis, dtype, a, s);
     v = NIR_VARIANT_PENCIL;   // per-point factors or M > kDenseMaxM: the register-pencil kernel
   }
@@ -397,7 +398,7 @@ nir_status nir_basis_create(int32_t shape, int32_t P, int32_t Q, nir_basis** out
       return st;
     }
   }
-  if (b->shape != kHex && (st = build_dense_refs(b)) != NIR_OK) {
+  if (b->shape != kHex && ((st = build_dense_refs(b)) != NIR_OK || (st = build_grad_tables(b)) != NIR_OK)) {
     nir_basis_destroy(b);
     return st;
   }
@@ -416,6 +417,8 @@ nir_status nir_basis_destroy(nir_basis* b) {
   if (b->dense64) (void)hipFree(b->dense64);
   if (b->dense32) (void)hipFree(b->dense32);
   if (b->dense16) (void)hipFree(b->dense16);
+  if (b->grad64) (void)hipFree(b->grad64);
+  if (b->grad32) (void)hipFree(b->grad32);
   delete b;
   return NIR_OK;
 }

@@ -11,11 +11,9 @@
 // a dense GEMM with K = 7 M that the FP64 matrix instructions run directly; the scaled A operand
 // is formed in registers from X staged in LDS.  The reference matrices come from the validated
 // sum-factorised generic kernel applied to unit vectors at basis creation (build_dense_refs).
+// Tetrahedra, whose modes' gradients have one degree less in every direction, take fewer operations
+// through them (helm_grad.hip) and use this form in the FP16-split variant only.
 // FP32 batches run the same GEMM on the FP32 matrix instructions with FP32 copies of the matrices.
-//
-// Operand layouts (checked on the device): lane l holds A[l%16][l/16] and B[l/16][l%16] in both
-// v_mfma_f64_16x16x4f64 and v_mfma_f32_16x16x4f32; the four results of lane l are
-// D[4v + l/16][l%16] (FP64) and D[4(l/16) + v][l%16] (FP32), v = 0..3.
 //
 // FP16-split variant (FP32 storage, NIR_MATH_F16SPLIT): the same GEMM as compensated FP16 products
 // on v_mfma_f32_16x16x16f16 (lane l holds A[l%16][4(l/16)+v], B[4(l/16)+v][l%16] and
@@ -31,27 +29,10 @@
 #include <vector>
 
 #include "generic_ops.h"
+#include "mfma_tile.h"
 #include "nir_internal.h"
 
 namespace nir {
-
-template <class T>
-using dense_v4 = T __attribute__((ext_vector_type(4)));
-
-template <class T>
-__device__ __forceinline__ dense_v4<T> dense_mfma(T a, T b, dense_v4<T> c) {
-  if constexpr (sizeof(T) == 8)
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-// row of result v of lane group lk (= l / 16) within a 16 x 16 tile
-template <class T>
-__device__ __forceinline__ int dense_drow(int v, int lk) {
-  return sizeof(T) == 8 ? 4 * v + lk : 4 * lk + v;
-}
-
-constexpr int dense_ceil(int a, int b) { return (a + b - 1) / b; }
 
 // The 4 wavefronts of a block form a WR x WC grid over the block's RT row tiles and NCT column
 // tiles; WC is the largest of 4, 2, 1 that splits the column tiles most evenly (each wave then
@@ -205,14 +186,14 @@ static nir_status launch_dense_shape(const nir_basis* b, int dtype, const OpArgs
 #undef NIR_CASE
 }
 
-// dense apply of an affine batch (per-element factors helm[nelmt][7]), FP64 or FP32
+// dense apply of an affine batch (per-element factors helm[nelmt][7]) of prisms or pyramids, FP64 or
+// FP32 (tetrahedra run launch_helm_grad)
 nir_status launch_helm_dense(const nir_basis* b, int dtype, const OpArgs& a, hipStream_t s) {
   if (!b->dense64) return fail(NIR_ENOTSUP, "no reference matrices for this basis");
   switch (b->shape) {
     case kPrism: return launch_dense_shape<kPrism>(b, dtype, a, s);
-    case kTet: return launch_dense_shape<kTet>(b, dtype, a, s);
     case kPyr: return launch_dense_shape<kPyr>(b, dtype, a, s);
-    default: return fail(NIR_ENOTSUP, "the dense apply covers the collapsed shapes");
+    default: return fail(NIR_ENOTSUP, "the dense apply covers prisms and pyramids");
   }
 }
 

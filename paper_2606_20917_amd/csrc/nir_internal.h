@@ -150,6 +150,10 @@ struct nir_basis {
   // in the B layout of v_mfma_f32_16x16x16f16 (hi block, then lo block), and the 1 / sigma_c
   void* dense16 = nullptr;
   float dense_inv[7] = {1, 1, 1, 1, 1, 1, 1};
+  // tetrahedra: the modes' reference gradients in an orthonormal basis, as the B operands of the
+  // affine apply (helm_grad.hip)
+  double* grad64 = nullptr;
+  float* grad32 = nullptr;
   const void* table_dev[NIR_TAB_COUNT];
 };
 
@@ -240,6 +244,10 @@ nir_status launch_helm_dense(const nir_basis* b, int dtype, const OpArgs& a, hip
 // the same GEMM as FP16-split compensated products on the FP16 matrix cores (FP32 storage)
 nir_status launch_helm_dense_f16split(const nir_basis* b, const OpArgs& a, hipStream_t s);
 nir_status build_dense_refs(nir_basis* b);
+// the same operator of affine tetrahedra through the modes' gradients (helm_grad.hip), whose tables
+// build_grad_tables places in the basis
+nir_status launch_helm_grad(const nir_basis* b, int dtype, const OpArgs& a, hipStream_t s);
+nir_status build_grad_tables(nir_basis* b);
 // the fused Helmholtz apply with the currently selected kernel variant (native contractions)
 bool helm_gathers(const nir_basis* basis, int dtype);
 nir_status launch_helm_auto(const nir_basis* basis, int dtype, int deformed, const OpArgs& a, hipStream_t s);
