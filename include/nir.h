@@ -263,7 +263,7 @@ nir_status nir_helmholtz_apply_nodal(const nir_batch* batch, const nir_basis* ba
  *                         orders compiled into the persistent kernel);
  *   NIR_MIXED_PER_BATCH   one launch per batch with its standalone kernel (the variant selected
  *                         for its (shape, P, dtype) when the graph is captured), spread over
- *                         four parallel graph branches balanced by bytes;
+ *                         three parallel graph branches balanced by bytes;
  *   NIR_MIXED_AUTO        (default) the first apply times both and keeps the faster; plans
  *                         with a batch of P > 8 use NIR_MIXED_PER_BATCH.
  * Results of both equal the per-batch nir_helmholtz_apply launches (the same device code per

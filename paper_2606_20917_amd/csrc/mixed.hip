@@ -19,7 +19,7 @@
 //
 // A second strategy is kept beside it: one hipGraph of per-batch launches, each with the
 // standalone kernel of its (shape, P) (own block size, LDS and register budget), spread over
-// up to four parallel graph branches balanced by bytes, so the launches overlap and fill each
+// up to three parallel graph branches balanced by bytes, so the launches overlap and fill each
 // other's tails.  The persistent kernel pays for its single launch with the union of the
 // item types' resources (LDS and registers of the largest); with the strategy left to the
 // plan (the default), the first apply times both and keeps the faster.
@@ -122,9 +122,13 @@ struct nir_mixed_plan {
   int strategy_req = NIR_MIXED_AUTO;   // requested strategy
   int strategy = 0;                    // strategy of the captured graph (0 before the first apply)
   bool persistent_ok = true;           // every batch has P <= kMixedMaxP
-  static constexpr int kBranches = 4;
-  hipStream_t aux[kBranches] = {nullptr, nullptr, nullptr, nullptr};
-  hipEvent_t fork = nullptr, join[kBranches] = {nullptr, nullptr, nullptr, nullptr};
+  // three branches: with four the graph's queues and the caller's share the four hardware queues.
+  // 100,000 elements of orders 3..8 (18 batches), us with 1, 2, 3, 4, 6 branches: FP32 378, 316, 274,
+  // 298, 303; FP64 626, 539, 501, 532, 542.  Branches balanced by time instead of bytes, or captured
+  // largest first, were 0-9 % slower; the same launches on plain streams 282-336 and 544-589
+  static constexpr int kBranches = 3;
+  hipStream_t aux[kBranches] = {};
+  hipEvent_t fork = nullptr, join[kBranches] = {};
   std::vector<int> branch_of;          // per-batch strategy: branch of each batch
   double ms_persistent = -1.0, ms_per_batch = -1.0;
 };
@@ -324,7 +328,7 @@ nir_status nir_mixed_plan_create(int32_t nbatch, const nir_batch* batches, const
   }
   std::stable_sort(order.begin(), order.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
   pl->branch_of.assign(nbatch, 0);
-  int64_t load[nir_mixed_plan::kBranches] = {0, 0, 0, 0};
+  int64_t load[nir_mixed_plan::kBranches] = {};
   for (const auto& o : order) {
     int k = int(std::min_element(load, load + nir_mixed_plan::kBranches) - load);
     pl->branch_of[o.second] = k;
