@@ -381,7 +381,8 @@ nir_status nir_cg_plan_destroy(nir_cg_plan* plan);
  * (shape, P, dtype) is library-global state (one int per combination, set atomically), used by
  * nir_helmholtz_apply and by the CG plans' element apply:
  *   NIR_VARIANT_AUTO       built-in default (a pencil kernel per shape; for hexahedra the
- *                          per-order choice measured fastest on MI355X)
+ *                          per-order choice measured fastest on MI355X, with per-element factors
+ *                          (deformed = 0) NIR_VARIANT_PENCIL_EO at every order, or its SPLIT form)
  *   NIR_VARIANT_GENERIC    LDS-staged kernel, threads over points/modes (any shape)
  *   NIR_VARIANT_PENCIL     register-pencil kernel with uniform basis operands (any shape; on
  *                          prisms, tetrahedra and pyramids the contractions whose 1-D factor
@@ -420,7 +421,8 @@ typedef enum { NIR_VARIANT_AUTO = 0, NIR_VARIANT_GENERIC = 1, NIR_VARIANT_PENCIL
                NIR_VARIANT_PENCIL_SPLIT = 6, NIR_VARIANT_PENCIL_GP = 7, NIR_VARIANT_PENCIL_SPLIT_GP = 8,
                NIR_VARIANT_PENCIL_EO = 9, NIR_VARIANT_PENCIL_EO_SPLIT = 10, NIR_VARIANT_DENSE = 11 } nir_variant;
 nir_status nir_set_helmholtz_variant(int32_t shape, int32_t P, int32_t dtype, int32_t variant);
-/* The variant a call with these parameters would run now (never NIR_VARIANT_AUTO); -1 if invalid. */
+/* The variant a call with these parameters and per-point factors would run now (never NIR_VARIANT_AUTO;
+ * NIR_VARIANT_DENSE stands for the choice it makes); -1 if invalid. */
 int32_t nir_get_helmholtz_variant(int32_t shape, int32_t P, int32_t dtype);
 /* Autotuner: times every variant applicable to the batch's shape on the caller's operands
  * (one warm-up and `reps` timed applies each, hipEvents on `stream`; coef_out is overwritten),

@@ -93,7 +93,7 @@ static nir_status native_only(const nir_batch* b) {
 // variant table [shape][P][dtype]; 0 = auto
 static std::atomic<int> g_variant[4][kMaxP + 1][2];
 
-static int resolve_variant(int shape, int P, int dtype) {
+static int resolve_variant(int shape, int P, int dtype, int deformed = 1) {
   const int v = g_variant[shape][P][dtype].load(std::memory_order_relaxed);
   if (v != NIR_VARIANT_AUTO) return v;
   // the reference-matrix GEMM on the matrix cores for affine batches (the pencil kernel runs the
@@ -111,6 +111,11 @@ static int resolve_variant(int shape, int P, int dtype) {
                    EO = NIR_VARIANT_PENCIL_EO, EOS = NIR_VARIANT_PENCIL_EO_SPLIT;
   static const int8_t def64[kMaxP + 1] = {0, 0, EO, EO, PF, EO, GP, EO, SGP, EOS, EO};
   static const int8_t def32[kMaxP + 1] = {0, 0, EO, EO, EO, EO, EO, EO, EO, EO, EO};
+  // per-element factors: the folded kernels at every order, their traffic being a seventh and the
+  // contractions what bounds them (32^3 affine hexes in FP64, the tables above -> folded: P = 4
+  // 58 -> 25, P = 6 104 -> 74, P = 8 276 -> 169 us); the two-plane exchange pays at P = 6 in FP64
+  // (82 -> 74 us) and is within 1 % elsewhere
+  if (!deformed) return dtype == NIR_F64 && P == 6 ? EOS : EO;
   return dtype == NIR_F64 ? def64[P] : def32[P];
 }
 
@@ -122,7 +127,7 @@ bool helm_gathers(const nir_basis* basis, int dtype) {
 
 // the fused Helmholtz apply with the selected kernel variant (native contractions)
 nir_status launch_helm_auto(const nir_basis* basis, int dtype, int deformed, const OpArgs& a, hipStream_t s) {
-  int v = resolve_variant(basis->shape, basis->P, dtype);
+  int v = resolve_variant(basis->shape, basis->P, dtype, deformed);
   if (v == NIR_VARIANT_DENSE) {
     if (basis->shape == kTet && !deformed && basis->grad64) return launch_helm_grad(basis, dtype, a, s);
     if (basis->shape != kHex && !deformed && basis->dense64) return launch_helm_dense(basis, dtype, a, s);

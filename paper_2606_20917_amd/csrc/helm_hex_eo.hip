@@ -24,10 +24,19 @@ k_helm_hex_eo(const T* __restrict__ tabs, const T* __restrict__ x, T* __restrict
                                                            int64_t(blockIdx.x) * E, lds, nullptr, nullptr, nullptr, map);
 }
 
+// Elements per block on per-element factors, where the sweeps and their barriers bound the kernel:
+// one element at P = 7, whose 64 pencils are one wavefront (32^3 hexes, blocks of 4 -> 1: FP64 121
+// -> 100 us, FP32 69 -> 57 us), and at P = 9 and 10 (FP64 P = 10, blocks of 2 -> 1: 478 -> 436 us);
+// otherwise near 128 pencils (P = 4, 10 -> 5 elements: FP64 26.7 -> 24.8 us) or all that fit
+template <int P>
+constexpr int eo_affine_elems() {
+  return P == 7 || P >= 9 ? 1 : (P == 3 ? 4 : (P == 4 ? 5 : (P == 5 ? 3 : 256 / ((P + 1) * (P + 1)))));
+}
+
 template <int P, class T, bool DEF, bool TP>
 static void launch_eo_cfg(const T* tb, const T* x, T* y, const T* helm, const T* wq, T lam, int64_t nelmt,
                           const int32_t* map, hipStream_t s) {
-  constexpr int E = DEF ? hex_block_elems<P, T>(TP ? kFamEOS : kFamEO) : 256 / ((P + 1) * (P + 1));
+  constexpr int E = DEF ? hex_block_elems<P, T>(TP ? kFamEOS : kFamEO) : eo_affine_elems<P>();
   using D = HexPencilDims<P, T, E, TP>;
   const int64_t nb = (nelmt + E - 1) / E;
   hipLaunchKernelGGL((k_helm_hex_eo<P, T, DEF, E, TP>), dim3(static_cast<unsigned>(nb)), dim3(D::BLOCK), 0, s, tb,
