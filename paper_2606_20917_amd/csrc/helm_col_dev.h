@@ -71,6 +71,19 @@ __device__ __forceinline__ const_ptr<T> fresh_table_after(const T* p, const D& d
   return (const_ptr<T>)u;
 }
 
+// Rows of n values (factors and derivatives together) that an unrolled sweep requests together: as
+// many as 64 SGPRs hold where few wavefronts share a SIMD, since a sweep of one row at a time is a
+// chain of scalar loads.  24^3 cubes, one row -> batches: FP64 pyramids at P = 5 289 -> 278 us, P =
+// 10 1042 -> 1021; tetrahedra at P = 8 974 -> 954; FP32 pyramids at P = 9 841 -> 815, tetrahedra at
+// P = 10 1310 -> 1266.  One row elsewhere, where other wavefronts cover the chain (FP64 tetrahedra
+// at P = 4 122.4 -> 124.3 us, FP32 at P = 6 199 -> 209).
+template <int SHAPE, int P, class T>
+constexpr int col_row_batch(int n) {
+  const bool few = sizeof(T) == 8 ? P >= 5 : P >= 9 || SHAPE == kPyr;
+  const int d = n * int(sizeof(T)) / 4;
+  return !few || d > 32 ? 1 : 64 / d;
+}
+
 // Completes the N values of `v` before the next volatile asm (the next row's fresh_table): in an
 // unrolled sweep the loads of row k+1 then wait for all the products of row k, so only about one
 // row of factors is live in SGPRs.
@@ -289,11 +302,16 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
           for (int r = 0; r < nr; ++r) c[r] = (sl == 0 && r == 1) ? T(0) : Ls[m0 + r];   // vertex mode apart
           // one row of nr terms per point k (transposed table): only that row is live in SGPRs
           constexpr int off = col_a_off(SHAPE, P, sl);
+          constexpr int RB = col_row_batch<SHAPE, P, T>((BWD ? 1 : 2) * nr);
+          const_ptr<T> f0 = nullptr, df0 = nullptr;
 #pragma unroll
           for (int k = 0; k < Q; ++k) {
-            const T dep = k > 0 ? a0[k - 1] : c[0];
-            const const_ptr<T> f = fresh_table_after(tb.T3t, dep) + (off + k * nr);
-            const const_ptr<T> df = fresh_table_after(tb.dT3t, dep) + (off + k * nr);
+            if (k % RB == 0) {
+              const T dep = k > 0 ? a0[k - 1] : c[0];
+              f0 = fresh_table_after(tb.T3t, dep) + off;
+              df0 = fresh_table_after(tb.dT3t, dep) + off;
+            }
+            const const_ptr<T> f = f0 + k * nr, df = df0 + k * nr;
             T v0 = T(0), v1 = T(0);
 #pragma unroll
             for (int r = 0; r < nr; ++r) {
@@ -326,11 +344,16 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
 #pragma unroll
             for (int r = 0; r < nr; ++r) c[r] = (sl == 0 && r == 1) ? T(0) : oL[m0 + r];
             constexpr int off = col_a_off(SHAPE, P, sl);
+            constexpr int RB = col_row_batch<SHAPE, P, T>((BWD ? 1 : 2) * nr);
+            const_ptr<T> f0 = nullptr, df0 = nullptr;
 #pragma unroll
             for (int k = 0; k < Q; ++k) {
-              const T dep = k > 0 ? o0[k - 1] : c[0];
-              const const_ptr<T> f = fresh_table_after(tb.T3t, dep) + (off + k * nr);
-              const const_ptr<T> df = fresh_table_after(tb.dT3t, dep) + (off + k * nr);
+              if (k % RB == 0) {
+                const T dep = k > 0 ? o0[k - 1] : c[0];
+                f0 = fresh_table_after(tb.T3t, dep) + off;
+                df0 = fresh_table_after(tb.dT3t, dep) + off;
+              }
+              const const_ptr<T> f = f0 + k * nr, df = df0 + k * nr;
               T v0 = T(0), v1 = T(0);
 #pragma unroll
               for (int r = 0; r < nr; ++r) {
@@ -373,11 +396,16 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
           for (int r = 0; r < nr; ++r) c[r] = Ls[m0 + r];
           if constexpr (nt > nr) c[nr] = Ls[MO::m0(0, 0) + q * P + 1];
           // one row of terms per point k (transposed table): only that row is live in SGPRs
+          constexpr int RB = col_row_batch<SHAPE, P, T>((BWD ? 1 : 2) * nt);
+          const_ptr<T> f0 = nullptr, df0 = nullptr;
 #pragma unroll
           for (int k = 0; k < Q; ++k) {
-            const T dep = k > 0 ? a0[k - 1] : c[0];
-            const const_ptr<T> f = fresh_table_after(tb.T3t, dep) + (off + k * nt);
-            const const_ptr<T> df = fresh_table_after(tb.dT3t, dep) + (off + k * nt);
+            if (k % RB == 0) {
+              const T dep = k > 0 ? a0[k - 1] : c[0];
+              f0 = fresh_table_after(tb.T3t, dep) + off;
+              df0 = fresh_table_after(tb.dT3t, dep) + off;
+            }
+            const const_ptr<T> f = f0 + k * nt, df = df0 + k * nt;
             T v0 = T(0), v1 = T(0);
 #pragma unroll
             for (int r = 0; r < nt; ++r) {
@@ -441,11 +469,16 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
           constexpr int nt = col_b_terms(SHAPE, P, pc);
           constexpr int off = col_b_off(SHAPE, P, pc);
           static_assert(nt == nq + (X ? 1 : 0), "B terms");
+          constexpr int RB = col_row_batch<SHAPE, P, T>((BWD ? 1 : 2) * nt);
+          const_ptr<T> f0 = nullptr, df0 = nullptr;
   #pragma unroll
           for (int j = 0; j < Q; ++j) {
-            const T dep = j > 0 ? b0[j - 1] : av[0];
-            const const_ptr<T> f = fresh_table_after(tb.T2t, dep) + (off + j * nt);
-            const const_ptr<T> df = fresh_table_after(tb.dT2t, dep) + (off + j * nt);
+            if (j % RB == 0) {
+              const T dep = j > 0 ? b0[j - 1] : av[0];
+              f0 = fresh_table_after(tb.T2t, dep) + off;
+              df0 = fresh_table_after(tb.dT2t, dep) + off;
+            }
+            const const_ptr<T> f = f0 + j * nt, df = df0 + j * nt;
             T v0 = T(0), v1 = T(0), v2 = T(0);
   #pragma unroll
             for (int q = 0; q < nt; ++q) {
@@ -469,10 +502,12 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
           T ea[NE], oa[NO], eb[NE], ob[NO];
           eo_fold<P>(av, ea, oa);
           if constexpr (!BWD) eo_fold<P>(bv, eb, ob);
+          constexpr int RB = col_row_batch<SHAPE, P, T>(ROW);
+          const_ptr<T> rows = nullptr;
 #pragma unroll
           for (int h = 0; h < H; ++h) {
-            const T dep = h > 0 ? b0[h - 1] : av[0];
-            const HexTabEO<P, T> tk{fresh_table_after(tb.eo, dep) + h * ROW};
+            if (h % RB == 0) rows = fresh_table_after(tb.eo, h > 0 ? b0[h - 1] : av[0]);
+            const HexTabEO<P, T> tk{rows + h * ROW};
             const bool mid = F::MID && h == H - 1;
             T S0, A0, SD = T(0), AD = T(0), S2 = T(0), A2 = T(0);
             eo_val(tk, ea, oa, S0, A0, mid);
@@ -894,11 +929,16 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
           constexpr int off = col_b_off(SHAPE, P, pc);
   #pragma unroll
           for (int q = 0; q < nt; ++q) s0[q] = s1[q] = T(0);
+          constexpr int RB = col_row_batch<SHAPE, P, T>((IPR ? 1 : 2) * nt);
+          const_ptr<T> f0 = nullptr, df0 = nullptr;
   #pragma unroll
           for (int j = 0; j < Q; ++j) {
-            const T dep = j > 0 ? (IPR ? s0[nt - 1] : s1[nt - 1]) : tv0[0];
-            const const_ptr<T> f = fresh_table_after(tb.T2t, dep) + (off + j * nt);
-            const const_ptr<T> df = fresh_table_after(tb.dT2t, dep) + (off + j * nt);
+            if (j % RB == 0) {
+              const T dep = j > 0 ? (IPR ? s0[nt - 1] : s1[nt - 1]) : tv0[0];
+              f0 = fresh_table_after(tb.T2t, dep) + off;
+              df0 = fresh_table_after(tb.dT2t, dep) + off;
+            }
+            const const_ptr<T> f = f0 + j * nt, df = df0 + j * nt;
   #pragma unroll
             for (int q = 0; q < nt; ++q) {
               s0[q] += f[q] * tv0[j];
@@ -916,10 +956,12 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
           for (int k2 = 0; k2 < NE; ++k2) E0[k2] = E1[k2] = T(0);
 #pragma unroll
           for (int k2 = 0; k2 < NO; ++k2) O0[k2] = O1[k2] = T(0);
+          constexpr int RB = col_row_batch<SHAPE, P, T>(ROW);
+          const_ptr<T> rows = nullptr;
 #pragma unroll
           for (int h = 0; h < H; ++h) {
-            const T dep = h > 0 ? (IPR ? O0[NO - 1] : O1[NO - 1]) : tv0[0];
-            const HexTabEO<P, T> tk{fresh_table_after(tb.eo, dep) + h * ROW};
+            if (h % RB == 0) rows = fresh_table_after(tb.eo, h > 0 ? (IPR ? O0[NO - 1] : O1[NO - 1]) : tv0[0]);
+            const HexTabEO<P, T> tk{rows + h * ROW};
             const bool mid = F::MID && h == H - 1;
             T sv, dv;
             eo_pair<P>(tv0, h, mid, sv, dv);
@@ -995,11 +1037,16 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
           constexpr int off = col_a_off(SHAPE, P, sl);
 #pragma unroll
           for (int r = 0; r < nr; ++r) yv[r] = T(0);
+          constexpr int RB = col_row_batch<SHAPE, P, T>((IPR ? 1 : 2) * nr);
+          const_ptr<T> f0 = nullptr, df0 = nullptr;
 #pragma unroll
           for (int k = 0; k < Q; ++k) {
-            const T dep = k > 0 ? yv[0] : sv0[0];
-            const const_ptr<T> f = fresh_table_after(tb.T3t, dep) + (off + k * nr);
-            const const_ptr<T> df = fresh_table_after(tb.dT3t, dep) + (off + k * nr);
+            if (k % RB == 0) {
+              const T dep = k > 0 ? yv[0] : sv0[0];
+              f0 = fresh_table_after(tb.T3t, dep) + off;
+              df0 = fresh_table_after(tb.dT3t, dep) + off;
+            }
+            const const_ptr<T> f = f0 + k * nr, df = df0 + k * nr;
 #pragma unroll
             for (int r = 0; r < nr; ++r) {
               if (sl == 0 && r == 1) continue;
@@ -1038,11 +1085,16 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
             constexpr int off = col_a_off(SHAPE, P, sl);
 #pragma unroll
             for (int r = 0; r < nr; ++r) oy[r] = T(0);
+            constexpr int RB = col_row_batch<SHAPE, P, T>((IPR ? 1 : 2) * nr);
+            const_ptr<T> f0 = nullptr, df0 = nullptr;
 #pragma unroll
             for (int k = 0; k < Q; ++k) {
-              const T dep = k > 0 ? oy[0] : sv0[0];
-              const const_ptr<T> f = fresh_table_after(tb.T3t, dep) + (off + k * nr);
-              const const_ptr<T> df = fresh_table_after(tb.dT3t, dep) + (off + k * nr);
+              if (k % RB == 0) {
+                const T dep = k > 0 ? oy[0] : sv0[0];
+                f0 = fresh_table_after(tb.T3t, dep) + off;
+                df0 = fresh_table_after(tb.dT3t, dep) + off;
+              }
+              const const_ptr<T> f = f0 + k * nr, df = df0 + k * nr;
 #pragma unroll
               for (int r = 0; r < nr; ++r) {
                 if (sl == 0 && r == 1) continue;
@@ -1098,11 +1150,16 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
           constexpr int nt = col_a_terms(SHAPE, P, sl), off = col_a_off(SHAPE, P, sl);
 #pragma unroll
           for (int r = 0; r < nr; ++r) yv[r] = T(0);
+          constexpr int RB = col_row_batch<SHAPE, P, T>((IPR ? 1 : 2) * nt);
+          const_ptr<T> f0 = nullptr, df0 = nullptr;
 #pragma unroll
           for (int k = 0; k < Q; ++k) {
-            const T dep = k > 0 ? yv[0] : sv0[0];
-            const const_ptr<T> f = fresh_table_after(tb.T3t, dep) + (off + k * nt);
-            const const_ptr<T> df = fresh_table_after(tb.dT3t, dep) + (off + k * nt);
+            if (k % RB == 0) {
+              const T dep = k > 0 ? yv[0] : sv0[0];
+              f0 = fresh_table_after(tb.T3t, dep) + off;
+              df0 = fresh_table_after(tb.dT3t, dep) + off;
+            }
+            const const_ptr<T> f = f0 + k * nt, df = df0 + k * nt;
 #pragma unroll
             for (int r = 0; r < nr; ++r) {
               if (p == 0 && r == 1) {
