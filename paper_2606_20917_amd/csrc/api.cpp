@@ -444,7 +444,6 @@ nir_status nir_basis_destroy(nir_basis* b) {
   if (b->dense32) (void)hipFree(b->dense32);
   if (b->dense16) (void)hipFree(b->dense16);
   if (b->grad64) (void)hipFree(b->grad64);
-  if (b->grad32) (void)hipFree(b->grad32);
   delete b;
   return NIR_OK;
 }

@@ -17,6 +17,7 @@
 // operand F is formed from LDS as it is read (nine multiply-adds for the operands of 3 CT2 tile
 // steps); B operands come from L2 two steps ahead.
 #include <cmath>
+#include <cstring>
 #include <type_traits>
 #include <vector>
 
@@ -286,6 +287,11 @@ static real jacobi(int n, real a, real b, real x) {   // P_n^{(a,b)}(x), three-t
   }
   return p;
 }
+static real ipow(real x, int n) {
+  real v = 1;
+  for (int k = 0; k < n; ++k) v *= x;
+  return v;
+}
 static real djacobi(int n, real a, real b, real x) { return n ? (n + a + b + 1) / 2 * jacobi(n - 1, a + 1, b + 1, x) : 0; }
 
 // the modified basis factor psi^b_pq (psi^a_q for p = 0) and its derivative
@@ -301,7 +307,7 @@ static void modified(int p, int q, real z, real* v, real* d) {
     }
     return;
   }
-  const real a = std::pow(l, real(p)), da = -real(p) / 2 * std::pow(l, real(p - 1));
+  const real da = -real(p) / 2 * ipow(l, p - 1), a = ipow(l, p);
   if (q == 0) {
     *v = a;
     *d = da;
@@ -323,7 +329,7 @@ static real integral(const Vec& w, const Vec& f, const Vec& g) {
 // The gradient tables of a tetrahedral basis (shape kTet with reference matrices): psi_g the
 // orthonormal polynomials of degree P - 2,
 //   psi_ijk = c P_i(eta1) ((1-eta2)/2)^i P_j^{(2i+1,0)}(eta2) ((1-eta3)/2)^{i+j} P_k^{(2i+2j+2,0)}(eta3).
-// Synchronous; the basis owns grad64 / grad32 afterwards.
+// Synchronous; the basis owns grad64 afterwards, which holds grad32 too.
 nir_status build_grad_tables(nir_basis* b) {
   if (b->shape != kTet || !b->dense64) return NIR_OK;
   const int P = b->P, M = b->M, G = (P - 1) * P * (P + 1) / 6, N = P + 3;
@@ -355,21 +361,19 @@ nir_status build_grad_tables(nir_basis* b) {
   };
   auto shifted = [&](int power, int deg, int alpha) {   // ((1-z)/2)^power P_deg^{(alpha,0)}
     Vec f(N);
-    for (int n = 0; n < N; ++n) f[n] = std::pow((1 - z[n]) / 2, real(power)) * jacobi(deg, alpha, 0, z[n]);
+    for (int n = 0; n < N; ++n) f[n] = ipow((1 - z[n]) / 2, power) * jacobi(deg, alpha, 0, z[n]);
     return f;
   };
   std::vector<double> t64(size_t(MK) * N1P + size_t(12) * NG * MP, 0.0);
   double* B1 = t64.data();
   double* B2 = B1 + size_t(MK) * N1P;
-  // factors of the expansion: eta1 psi^a_p, eta2 psi^b_pq, eta3 psi^b_cr, c = p + q
-  std::vector<Vec> a1(P), d1(P), a2(P * P), d2(P * P), a3(P * P), d3(P * P);
+  // factors of the expansion: eta1 psi^a_p, eta2 psi^b_pq, eta3 psi^b_cr, c = p + q, from the same rule
+  std::vector<Vec> a1(P), d1(P), a2(P * P), d2(P * P);
   for (int p = 0; p < P; ++p) {
     factor(0, p, a1[p], d1[p]);
-    for (int q = 0; p + q < P; ++q) {
-      factor(p, q, a2[p * P + q], d2[p * P + q]);
-      factor(p, q, a3[p * P + q], d3[p * P + q]);
-    }
+    for (int q = 0; p + q < P; ++q) factor(p, q, a2[p * P + q], d2[p * P + q]);
   }
+  Vec va(P * P), vd(P * P);
   int g = 0;
   for (int i = 0; i <= P - 2; ++i) {
     const Vec f1 = shifted(0, i, 0);
@@ -398,11 +402,10 @@ nir_status build_grad_tables(nir_basis* b) {
       for (int k = 0; i + j + k <= P - 2; ++k, ++g) {
         const Vec f3 = shifted(i + j, k, 2 * (i + j) + 2);
         const real c = 1 / std::sqrt(integral(w, f1, f1) * integral(w2v, f2, f2) * integral(w3v, f3, f3));
-        Vec va(P * P), vd(P * P);
         for (int s = 0; s < P; ++s)
           for (int r = 0; s + r < P; ++r) {
-            va[s * P + r] = c * integral(w3a, f3, a3[s * P + r]);
-            vd[s * P + r] = c * integral(w3v, f3, d3[s * P + r]);
+            va[s * P + r] = c * integral(w3a, f3, a2[s * P + r]);
+            vd[s * P + r] = c * integral(w3v, f3, d2[s * P + r]);
           }
         int m = 0;
         for (int p = 0; p < P; ++p)
@@ -422,11 +425,14 @@ nir_status build_grad_tables(nir_basis* b) {
       }
     }
   }
+  // one array: the FP64 tables, then the same in FP32
+  const size_t n = t64.size();
   const std::vector<float> t32(t64.begin(), t64.end());
+  t64.resize(n + (n + 1) / 2);
+  std::memcpy(t64.data() + n, t32.data(), n * sizeof(float));
   NIR_TRYS(hip_check(hipMalloc(&b->grad64, t64.size() * 8), "hipMalloc"));
-  NIR_TRYS(hip_check(hipMalloc(&b->grad32, t32.size() * 4), "hipMalloc"));
-  NIR_TRYS(hip_check(hipMemcpy(b->grad64, t64.data(), t64.size() * 8, hipMemcpyHostToDevice), "copy"));
-  return hip_check(hipMemcpy(b->grad32, t32.data(), t32.size() * 4, hipMemcpyHostToDevice), "copy");
+  b->grad32 = reinterpret_cast<float*>(b->grad64 + n);
+  return hip_check(hipMemcpy(b->grad64, t64.data(), t64.size() * 8, hipMemcpyHostToDevice), "copy");
 }
 
 }  // namespace nir

@@ -151,7 +151,7 @@ struct nir_basis {
   void* dense16 = nullptr;
   float dense_inv[7] = {1, 1, 1, 1, 1, 1, 1};
   // tetrahedra: the modes' reference gradients in an orthonormal basis, as the B operands of the
-  // affine apply (helm_grad.hip)
+  // affine apply (helm_grad.hip); grad32 lies in the same array
   double* grad64 = nullptr;
   float* grad32 = nullptr;
   const void* table_dev[NIR_TAB_COUNT];
