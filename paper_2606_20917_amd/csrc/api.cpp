@@ -97,9 +97,9 @@ static std::atomic<int> g_variant[4][kMaxP + 1][2];
 static int resolve_variant(int shape, int P, int dtype, int deformed = 1) {
   const int v = g_variant[shape][P][dtype].load(std::memory_order_relaxed);
   if (v != NIR_VARIANT_AUTO) return v;
-  // the reference-matrix GEMM on the matrix cores for affine batches (the pencil kernel runs the
-  // others): tetrahedra at every order (still 1.5x the pencil kernel at P = 10), prisms to P = 4
-  // and pyramids to P = 6, past which the pencil kernel is faster (measured on MI355X, 24^3 cubes)
+  // the matrix cores for affine batches of a size (dense_from; the pencil kernel runs the others):
+  // tetrahedra at every order, in the gradient form (40,000 at P = 10 in FP64: 491 us, the pencil
+  // kernel 629), prisms to P = 4 and pyramids to P = 6, past which the pencil kernel is faster
   if (shape == kTet || (shape == kPrism && P <= 4) || (shape == kPyr && P <= 6)) return NIR_VARIANT_DENSE;
   if (shape != kHex) return NIR_VARIANT_PENCIL;
   // defaults from a sweep of all variants, each with its tuned elements per block, on MI355X
@@ -441,8 +441,6 @@ nir_status nir_basis_destroy(nir_basis* b) {
   if (b->mfma_tabs) (void)hipFree(b->mfma_tabs);
   if (b->mfma_scale) (void)hipFree(b->mfma_scale);
   if (b->dense64) (void)hipFree(b->dense64);
-  if (b->dense32) (void)hipFree(b->dense32);
-  if (b->dense16) (void)hipFree(b->dense16);
   if (b->grad64) (void)hipFree(b->grad64);
   delete b;
   return NIR_OK;

@@ -39,9 +39,10 @@ constexpr int col_waves_target() {
 //   W in FP64: the compiler's own allocation (W = 2) fits two or three groups at P = 5, 6 and, on
 //        prisms, P = 8 and is 1-5 % faster than one forced to 128 VGPRs (prisms at P = 8: 298.5
 //        -> 290.4 us); P = 7 needs the 128 of W = 4 for its two groups
-//   W in FP32: 80 VGPRs (W = 6) let a second group of 9 or 10 wavefronts in at P = 9 and, on prisms,
-//        P = 10: 322 -> 252, 1060 -> 767 (tetrahedra 959 -> 766) and 414 -> 343 us; tetrahedra and
-//        pyramids at P = 10 spill there (678 -> 850 us) and keep one group
+//   W in FP32: 80 VGPRs (W = 6) let a second group of 9 or 10 wavefronts in at P = 9 (prisms 311 ->
+//        259, tetrahedra 959 -> 720, pyramids 1064 -> 848 us) and on prisms at P = 10 (414 -> 348);
+//        tetrahedra and pyramids at P = 10 spill there (half the mesh 678 -> 850 us) and keep one
+//        group.  W = 5 lets no second group in: the wavefronts of each start on the same SIMD
 struct ColCfg {
   int E, W;
 };

@@ -36,11 +36,12 @@
 // The contractions over Gauss-Lobatto points are folded by even-odd symmetry (eo_fold.h): B and B^T
 // of the prism and the pyramid, and C and C^T of affine elements.  With per-point factors C stays
 // unfolded: a pair of points holds twice the factors and values, about 30 FP64 registers more, and
-// the spills cost more than the arithmetic saved (tetrahedra at P = 6 in FP64 420 -> 663 us).  What
-// bounds it there is the factor stream against the sweeps that stream nothing, hence the first
+// the spills cost more than the arithmetic saved (tetrahedra at P = 6 in FP64 420 -> 663 us); where
+// it fits with two planes in LDS, the pairs' longer chain does (pyramids at P = 5 283 -> 312 us, prisms
+// at P = 8 287 -> 362).  What bounds it there is the factor stream against the sweeps that stream nothing, hence the first
 // point's factors in flight through A and B and buffer loads without address arithmetic.  24^3
 // cubes, FP64, before and after: prisms at P = 8 370 -> 287 us (3.4 -> 4.4 TB/s), at P = 10 824 ->
-// 642; pyramids at P = 5 321 -> 289, at P = 7 866 -> 617; tetrahedra at P = 7 749 -> 576 us.
+// 638; pyramids at P = 5 321 -> 282, at P = 7 866 -> 586; tetrahedra at P = 7 749 -> 548 us.
 //
 // LDS per element (values of T): one region of 3 P Q^2 values that holds, in turn, the
 // coefficients, the A rows, the B planes, the C^T planes, the B^T rows and the results;

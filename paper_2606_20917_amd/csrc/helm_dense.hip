@@ -370,46 +370,34 @@ nir_status launch_helm_dense_f16split(const nir_basis* b, const OpArgs& a, hipSt
 // The seven reference matrices of (shape, P), stacked [7 MP][MP] and zero-padded, in FP64 and an
 // FP32 copy: the generic Helmholtz kernel applied (lambda = 1, per-element factors) to 7 M unit
 // "elements", element (c, m) holding x = e_m and the factors g = e_c, gives row m of matrix c
-// (the matrices are symmetric).  Synchronous; the caller owns b->dense64 / b->dense32 afterwards.
+// (the matrices are symmetric).  Synchronous; the basis owns dense64 afterwards, which holds dense32 and dense16 too.
 nir_status build_dense_refs(nir_basis* b) {
   const int M = b->M, MP = (M + 15) / 16 * 16;
   if (M > kDenseMaxM) return NIR_OK;   // the sum-factorised kernels only
   const int64_t ne = int64_t(7) * M;
-  std::vector<double> hx(size_t(ne) * M, 0.0), hg(size_t(ne) * 7, 0.0), hy(size_t(ne) * M, 0.0);
+  // one device array: the unit vectors, their factors, the results
+  const size_t nx = size_t(ne) * M, ng = size_t(ne) * 7;
+  std::vector<double> hx(nx + ng, 0.0), hy(nx);
   for (int c = 0; c < 7; ++c)
     for (int m = 0; m < M; ++m) {
       const int64_t e = int64_t(c) * M + m;
       hx[size_t(e) * M + m] = 1.0;
-      hg[size_t(e) * 7 + c] = 1.0;
+      hx[nx + size_t(e) * 7 + c] = 1.0;
     }
-  double *dx = nullptr, *dg = nullptr, *dy = nullptr;
-  nir_status st = NIR_OK;
-  auto cleanup = [&]() {
-    if (dx) (void)hipFree(dx);
-    if (dg) (void)hipFree(dg);
-    if (dy) (void)hipFree(dy);
-  };
-  if ((st = hip_check(hipMalloc(&dx, hx.size() * 8), "hipMalloc")) != NIR_OK ||
-      (st = hip_check(hipMalloc(&dg, hg.size() * 8), "hipMalloc")) != NIR_OK ||
-      (st = hip_check(hipMalloc(&dy, hy.size() * 8), "hipMalloc")) != NIR_OK ||
-      (st = hip_check(hipMemcpy(dx, hx.data(), hx.size() * 8, hipMemcpyHostToDevice), "copy")) != NIR_OK ||
-      (st = hip_check(hipMemcpy(dg, hg.data(), hg.size() * 8, hipMemcpyHostToDevice), "copy")) != NIR_OK) {
-    cleanup();
-    return st;
-  }
+  double* dx = nullptr;
+  NIR_TRYS(hip_check(hipMalloc(&dx, (2 * nx + ng) * 8), "hipMalloc"));
   OpArgs a{};
   a.in0 = dx;
-  a.out0 = dy;
-  a.helm = dg;
+  a.helm = dx + nx;
+  a.out0 = dx + nx + ng;
   a.lambda = 1.0;
   a.nelmt = ne;
-  if ((st = launch_generic(b, kOpHelm, NIR_F64, 0, a, nullptr)) != NIR_OK ||
-      (st = hip_check(hipDeviceSynchronize(), "reference matrices")) != NIR_OK ||
-      (st = hip_check(hipMemcpy(hy.data(), dy, hy.size() * 8, hipMemcpyDeviceToHost), "copy")) != NIR_OK) {
-    cleanup();
-    return st;
-  }
-  cleanup();
+  nir_status st = hip_check(hipMemcpy(dx, hx.data(), hx.size() * 8, hipMemcpyHostToDevice), "copy");
+  if (st == NIR_OK) st = launch_generic(b, kOpHelm, NIR_F64, 0, a, nullptr);
+  if (st == NIR_OK) st = hip_check(hipDeviceSynchronize(), "reference matrices");
+  if (st == NIR_OK) st = hip_check(hipMemcpy(hy.data(), a.out0, nx * 8, hipMemcpyDeviceToHost), "copy");
+  (void)hipFree(dx);
+  if (st != NIR_OK) return st;
   std::vector<double> s64(size_t(7) * MP * MP, 0.0);
   std::vector<float> s32(s64.size(), 0.0f);
   for (int c = 0; c < 7; ++c)
@@ -445,14 +433,16 @@ nir_status build_dense_refs(nir_basis* b) {
             s16[half + o] = (_Float16)((a - float(hi)) * 2048.f);
           }
   }
-  if ((st = hip_check(hipMalloc(&b->dense64, s64.size() * 8), "hipMalloc")) != NIR_OK ||
-      (st = hip_check(hipMalloc(&b->dense32, s32.size() * 4), "hipMalloc")) != NIR_OK ||
-      (st = hip_check(hipMalloc(&b->dense16, s16.size() * 2), "hipMalloc")) != NIR_OK ||
-      (st = hip_check(hipMemcpy(b->dense64, s64.data(), s64.size() * 8, hipMemcpyHostToDevice), "copy")) != NIR_OK ||
-      (st = hip_check(hipMemcpy(b->dense32, s32.data(), s32.size() * 4, hipMemcpyHostToDevice), "copy")) != NIR_OK ||
-      (st = hip_check(hipMemcpy(b->dense16, s16.data(), s16.size() * 2, hipMemcpyHostToDevice), "copy")) != NIR_OK)
-    return st;
-  return NIR_OK;
+  // one array: FP64, FP32, FP16 (MP^2 is a multiple of 256, so each part is aligned)
+  const size_t n64 = s64.size() * 8, n32 = s32.size() * 4, n16 = s16.size() * 2;
+  std::vector<char> all(n64 + n32 + n16);
+  std::memcpy(all.data(), s64.data(), n64);
+  std::memcpy(all.data() + n64, s32.data(), n32);
+  std::memcpy(all.data() + n64 + n32, s16.data(), n16);
+  NIR_TRYS(hip_check(hipMalloc(&b->dense64, all.size()), "hipMalloc"));
+  b->dense32 = reinterpret_cast<float*>(reinterpret_cast<char*>(b->dense64) + n64);
+  b->dense16 = reinterpret_cast<char*>(b->dense64) + n64 + n32;
+  return hip_check(hipMemcpy(b->dense64, all.data(), all.size(), hipMemcpyHostToDevice), "copy");
 }
 
 }  // namespace nir

@@ -373,7 +373,30 @@ nir_status build_grad_tables(nir_basis* b) {
     factor(0, p, a1[p], d1[p]);
     for (int q = 0; p + q < P; ++q) factor(p, q, a2[p * P + q], d2[p * P + q]);
   }
-  Vec va(P * P), vd(P * P);
+  // eta3 integrals of psi_ijk: of s = i + j and k alone, the norm's share included
+  std::vector<Vec> va(P * P), vd(P * P);
+  for (int sl = 0; sl <= P - 2; ++sl)
+    for (int k = 0; sl + k <= P - 2; ++k) {
+      const Vec f3 = shifted(sl, k, 2 * sl + 2);
+      const real c3 = 1 / std::sqrt(integral(w3v, f3, f3));
+      Vec fa(N), fv(N), &a = va[sl * P + k], &d = vd[sl * P + k];
+      for (int n = 0; n < N; ++n) {
+        fa[n] = c3 * f3[n] * w3a[n];
+        fv[n] = c3 * f3[n] * w3v[n];
+      }
+      a.resize(P * P);
+      d.resize(P * P);
+      for (int t = 0; t < P; ++t)
+        for (int r = 0; t + r < P; ++r) {
+          real sa = 0, sd = 0;
+          for (int n = 0; n < N; ++n) {
+            sa += fa[n] * a2[t * P + r][n];
+            sd += fv[n] * d2[t * P + r][n];
+          }
+          a[t * P + r] = sa;
+          d[t * P + r] = sd;
+        }
+    }
   int g = 0;
   for (int i = 0; i <= P - 2; ++i) {
     const Vec f1 = shifted(0, i, 0);
@@ -389,38 +412,32 @@ nir_status build_grad_tables(nir_basis* b) {
     }
     for (int j = 0; i + j <= P - 2; ++j) {
       const Vec f2 = shifted(i, j, 2 * i + 1);
-      Vec v2(P * P + 1), c2(P * P + 1), dd2(P * P + 1), x2(P * P + 1);   // index P^2: the constant in eta2
-      for (int k = 0; k <= P * P; ++k) {
-        if (k < P * P && k / P + k % P >= P) continue;
-        const Vec& v = k < P * P ? a2[k] : one;
-        const Vec& d = k < P * P ? d2[k] : zero;
-        v2[k] = integral(w2v, f2, v);
-        c2[k] = integral(w2a, f2, v);
-        dd2[k] = integral(w2v, f2, d);
-        x2[k] = integral(w2x, f2, d);
+      const real c12 = 1 / std::sqrt(integral(w, f1, f1) * integral(w2v, f2, f2));
+      // the eta1 and eta2 parts of the three derivatives, per (p,q) (index P^2: the apex mode (0,0,1)):
+      // D_0 = e0 va, D_1 = e1 va, D_2 = e2 va + ev vd
+      Vec e0(P * P + 1), e1(P * P + 1), e2(P * P + 1), ev(P * P + 1);
+      for (int t = 0; t <= P * P; ++t) {
+        const bool apex = t == P * P;
+        if (!apex && t / P + t % P >= P) continue;
+        const Vec& v = apex ? one : a2[t];
+        const Vec& d = apex ? zero : d2[t];
+        const int k1 = apex || t == 1 ? P : t / P;
+        const real c2 = c12 * integral(w2a, f2, v), A = x1[k1] * c2 / 2;
+        e0[t] = dd1[k1] * c2;
+        e1[t] = A + 2 * v1[k1] * c12 * integral(w2v, f2, d);
+        e2[t] = A + v1[k1] * c12 * integral(w2x, f2, d);
+        ev[t] = v1[k1] * c12 * integral(w2v, f2, v);
       }
       for (int k = 0; i + j + k <= P - 2; ++k, ++g) {
-        const Vec f3 = shifted(i + j, k, 2 * (i + j) + 2);
-        const real c = 1 / std::sqrt(integral(w, f1, f1) * integral(w2v, f2, f2) * integral(w3v, f3, f3));
-        for (int s = 0; s < P; ++s)
-          for (int r = 0; s + r < P; ++r) {
-            va[s * P + r] = c * integral(w3a, f3, a2[s * P + r]);
-            vd[s * P + r] = c * integral(w3v, f3, d2[s * P + r]);
-          }
+        const Vec &a = va[(i + j) * P + k], &d = vd[(i + j) * P + k];
+        double* b2 = B2 + size_t(12 * (g / 4) + g % 4) * MP;
         int m = 0;
         for (int p = 0; p < P; ++p)
           for (int q = 0; p + q < P; ++q)
             for (int r = 0; p + q + r < P; ++r, ++m) {
-              const bool apex = p == 0 && q == 0 && r == 1;
-              const int k1 = apex || (p == 0 && q == 1) ? P : p, k2 = apex ? P * P : p * P + q, k3 = (p + q) * P + r;
-              const real A = x1[k1] * c2[k2] * va[k3] / 2;
-              const real D[3] = {dd1[k1] * c2[k2] * va[k3], A + 2 * v1[k1] * dd2[k2] * va[k3],
-                                 A + v1[k1] * x2[k2] * va[k3] + v1[k1] * v2[k2] * vd[k3]};
-              for (int a = 0; a < 3; ++a) {
-                const double v = double(D[a]);
-                B1[size_t(m) * N1P + a * G + g] = v;
-                B2[size_t((3 * (g / 4) + a) * 4 + g % 4) * MP + m] = v;
-              }
+              const int t = p == 0 && q == 0 && r == 1 ? P * P : p * P + q, k3 = (p + q) * P + r;
+              const double D[3] = {double(e0[t] * a[k3]), double(e1[t] * a[k3]), double(e2[t] * a[k3] + ev[t] * d[k3])};
+              for (int c = 0; c < 3; ++c) B1[size_t(m) * N1P + c * G + g] = b2[size_t(4 * c) * MP + m] = D[c];
             }
       }
     }

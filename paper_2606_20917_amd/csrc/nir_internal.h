@@ -143,7 +143,8 @@ struct nir_basis {
   float* mfma_tabs = nullptr;
   float* mfma_scale = nullptr;
   // collapsed shapes: the seven reference matrices of the affine Helmholtz operator, stacked
-  // [7 MP][MP] (MP = M rounded up to 16), FP64 and an FP32 copy (helm_dense.hip)
+  // [7 MP][MP] (MP = M rounded up to 16), FP64 and an FP32 copy (helm_dense.hip); dense32 and
+  // dense16 lie in the same array
   double* dense64 = nullptr;
   float* dense32 = nullptr;
   // the same, scaled per matrix by sigma_c into [1/2, 1) and split into FP16 hi and lo parts packed
