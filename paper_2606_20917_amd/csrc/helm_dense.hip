@@ -25,7 +25,6 @@
 // bound here, so the matrix cores' FP16 rate pays for the three products.
 #include <algorithm>
 #include <cmath>
-#include <cstring>
 #include <vector>
 
 #include "generic_ops.h"
@@ -398,8 +397,12 @@ nir_status build_dense_refs(nir_basis* b) {
   if (st == NIR_OK) st = hip_check(hipMemcpy(hy.data(), a.out0, nx * 8, hipMemcpyDeviceToHost), "copy");
   (void)hipFree(dx);
   if (st != NIR_OK) return st;
-  std::vector<double> s64(size_t(7) * MP * MP, 0.0);
-  std::vector<float> s32(s64.size(), 0.0f);
+  // one array: FP64, FP32, FP16 hi and lo (MP^2 is a multiple of 256, so each part is aligned)
+  const size_t half = size_t(7) * MP * MP;
+  std::vector<double> all(2 * half, 0.0);
+  double* s64 = all.data();
+  float* s32 = reinterpret_cast<float*>(s64 + half);
+  _Float16* s16 = reinterpret_cast<_Float16*>(s32 + half);
   for (int c = 0; c < 7; ++c)
     for (int m = 0; m < M; ++m)
       for (int n = 0; n < M; ++n) {
@@ -411,8 +414,6 @@ nir_status build_dense_refs(nir_basis* b) {
   // halves, packed per (matrix c, K block kb, column tile ct) as 64 lanes x 4 halves in the
   // instruction's B layout (lane l, half v: row 16 kb + 4(l/16) + v, column 16 ct + l%16)
   const int NKB = MP / 16, NCT = MP / 16;
-  const size_t half = size_t(7) * MP * MP;
-  std::vector<_Float16> s16(2 * half);
   for (int c = 0; c < 7; ++c) {
     double mx = 0.0;
     for (int m = 0; m < M; ++m)
@@ -433,16 +434,10 @@ nir_status build_dense_refs(nir_basis* b) {
             s16[half + o] = (_Float16)((a - float(hi)) * 2048.f);
           }
   }
-  // one array: FP64, FP32, FP16 (MP^2 is a multiple of 256, so each part is aligned)
-  const size_t n64 = s64.size() * 8, n32 = s32.size() * 4, n16 = s16.size() * 2;
-  std::vector<char> all(n64 + n32 + n16);
-  std::memcpy(all.data(), s64.data(), n64);
-  std::memcpy(all.data() + n64, s32.data(), n32);
-  std::memcpy(all.data() + n64 + n32, s16.data(), n16);
-  NIR_TRYS(hip_check(hipMalloc(&b->dense64, all.size()), "hipMalloc"));
-  b->dense32 = reinterpret_cast<float*>(reinterpret_cast<char*>(b->dense64) + n64);
-  b->dense16 = reinterpret_cast<char*>(b->dense64) + n64 + n32;
-  return hip_check(hipMemcpy(b->dense64, all.data(), all.size(), hipMemcpyHostToDevice), "copy");
+  NIR_TRYS(hip_check(hipMalloc(&b->dense64, all.size() * 8), "hipMalloc"));
+  b->dense32 = reinterpret_cast<float*>(b->dense64 + half);
+  b->dense16 = b->dense32 + half;
+  return hip_check(hipMemcpy(b->dense64, all.data(), all.size() * 8, hipMemcpyHostToDevice), "copy");
 }
 
 }  // namespace nir

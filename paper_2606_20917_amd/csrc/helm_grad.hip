@@ -17,7 +17,6 @@
 // operand F is formed from LDS as it is read (nine multiply-adds for the operands of 3 CT2 tile
 // steps); B operands come from L2 two steps ahead.
 #include <cmath>
-#include <cstring>
 #include <type_traits>
 #include <vector>
 
@@ -320,6 +319,11 @@ static void modified(int p, int q, real z, real* v, real* d) {
 
 // Values [n] of one factor at the rule's points; the integrals of two such vectors under a weight
 using Vec = std::vector<real>;
+static real dot(const Vec& f, const Vec& g) {
+  real s = 0;
+  for (size_t n = 0; n < f.size(); ++n) s += f[n] * g[n];
+  return s;
+}
 static real integral(const Vec& w, const Vec& f, const Vec& g) {
   real s = 0;
   for (size_t n = 0; n < w.size(); ++n) s += w[n] * f[n] * g[n];
@@ -338,7 +342,11 @@ nir_status build_grad_tables(nir_basis* b) {
   Vec z(N), w(N), one(N, real(1)), zero(N, real(0));
   for (int n = 0; n < N; ++n) {
     real x = -std::cos(std::acos(real(-1)) * (n + real(0.75)) / (N + real(0.5)));
-    for (int it = 0; it < 50; ++it) x -= jacobi(N, 0, 0, x) / djacobi(N, 0, 0, x);
+    for (int it = 0; it < 50; ++it) {
+      const real step = jacobi(N, 0, 0, x) / djacobi(N, 0, 0, x);
+      x -= step;
+      if (std::fabs(step) < real(1e-17)) break;   // the error after a step is of its square
+    }
     const real d = djacobi(N, 0, 0, x);
     z[n] = x;
     w[n] = 2 / ((1 - x * x) * d * d);
@@ -364,8 +372,10 @@ nir_status build_grad_tables(nir_basis* b) {
     for (int n = 0; n < N; ++n) f[n] = ipow((1 - z[n]) / 2, power) * jacobi(deg, alpha, 0, z[n]);
     return f;
   };
-  std::vector<double> t64(size_t(MK) * N1P + size_t(12) * NG * MP, 0.0);
-  double* B1 = t64.data();
+  // one array: the FP64 tables, then the same in FP32
+  const size_t nt = size_t(MK) * N1P + size_t(12) * NG * MP;
+  std::vector<double> tabs(nt + nt / 2, 0.0);
+  double* B1 = tabs.data();
   double* B2 = B1 + size_t(MK) * N1P;
   // factors of the expansion: eta1 psi^a_p, eta2 psi^b_pq, eta3 psi^b_cr, c = p + q, from the same rule
   std::vector<Vec> a1(P), d1(P), a2(P * P), d2(P * P);
@@ -388,13 +398,8 @@ nir_status build_grad_tables(nir_basis* b) {
       d.resize(P * P);
       for (int t = 0; t < P; ++t)
         for (int r = 0; t + r < P; ++r) {
-          real sa = 0, sd = 0;
-          for (int n = 0; n < N; ++n) {
-            sa += fa[n] * a2[t * P + r][n];
-            sd += fv[n] * d2[t * P + r][n];
-          }
-          a[t * P + r] = sa;
-          d[t * P + r] = sd;
+          a[t * P + r] = dot(fa, a2[t * P + r]);
+          d[t * P + r] = dot(fv, d2[t * P + r]);
         }
     }
   int g = 0;
@@ -415,18 +420,23 @@ nir_status build_grad_tables(nir_basis* b) {
       const real c12 = 1 / std::sqrt(integral(w, f1, f1) * integral(w2v, f2, f2));
       // the eta1 and eta2 parts of the three derivatives, per (p,q) (index P^2: the apex mode (0,0,1)):
       // D_0 = e0 va, D_1 = e1 va, D_2 = e2 va + ev vd
-      Vec e0(P * P + 1), e1(P * P + 1), e2(P * P + 1), ev(P * P + 1);
+      Vec e0(P * P + 1), e1(P * P + 1), e2(P * P + 1), ev(P * P + 1), fa(N), fv(N), fx(N);
+      for (int n = 0; n < N; ++n) {
+        fa[n] = c12 * w2a[n] * f2[n];
+        fv[n] = c12 * w2v[n] * f2[n];
+        fx[n] = c12 * w2x[n] * f2[n];
+      }
       for (int t = 0; t <= P * P; ++t) {
         const bool apex = t == P * P;
         if (!apex && t / P + t % P >= P) continue;
         const Vec& v = apex ? one : a2[t];
         const Vec& d = apex ? zero : d2[t];
         const int k1 = apex || t == 1 ? P : t / P;
-        const real c2 = c12 * integral(w2a, f2, v), A = x1[k1] * c2 / 2;
+        const real c2 = dot(fa, v), A = x1[k1] * c2 / 2;
         e0[t] = dd1[k1] * c2;
-        e1[t] = A + 2 * v1[k1] * c12 * integral(w2v, f2, d);
-        e2[t] = A + v1[k1] * c12 * integral(w2x, f2, d);
-        ev[t] = v1[k1] * c12 * integral(w2v, f2, v);
+        e1[t] = A + 2 * v1[k1] * dot(fv, d);
+        e2[t] = A + v1[k1] * dot(fx, d);
+        ev[t] = v1[k1] * dot(fv, v);
       }
       for (int k = 0; i + j + k <= P - 2; ++k, ++g) {
         const Vec &a = va[(i + j) * P + k], &d = vd[(i + j) * P + k];
@@ -442,14 +452,11 @@ nir_status build_grad_tables(nir_basis* b) {
       }
     }
   }
-  // one array: the FP64 tables, then the same in FP32
-  const size_t n = t64.size();
-  const std::vector<float> t32(t64.begin(), t64.end());
-  t64.resize(n + (n + 1) / 2);
-  std::memcpy(t64.data() + n, t32.data(), n * sizeof(float));
-  NIR_TRYS(hip_check(hipMalloc(&b->grad64, t64.size() * 8), "hipMalloc"));
-  b->grad32 = reinterpret_cast<float*>(b->grad64 + n);
-  return hip_check(hipMemcpy(b->grad64, t64.data(), t64.size() * 8, hipMemcpyHostToDevice), "copy");
+  float* t32 = reinterpret_cast<float*>(B1 + nt);
+  for (size_t k = 0; k < nt; ++k) t32[k] = float(B1[k]);
+  NIR_TRYS(hip_check(hipMalloc(&b->grad64, tabs.size() * 8), "hipMalloc"));
+  b->grad32 = reinterpret_cast<float*>(b->grad64 + nt);
+  return hip_check(hipMemcpy(b->grad64, tabs.data(), tabs.size() * 8, hipMemcpyHostToDevice), "copy");
 }
 
 }  // namespace nir
