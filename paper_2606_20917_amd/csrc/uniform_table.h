@@ -29,6 +29,15 @@ __device__ __forceinline__ const_ptr<T> fresh_table(const T* p) {
   return (const_ptr<T>)u;
 }
 
+// a pointer that is the same in every lane, moved into SGPRs
+template <class T>
+__device__ __forceinline__ const T* uniform_pointer(const T* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v))));
+  const uint32_t hi = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v >> 32))));
+  return reinterpret_cast<const T*>((uint64_t(hi) << 32) | uint64_t(lo));
+}
+
 // Row view of a direction-1 table in [point][mode] layout through a fresh pointer:
 // B(i, p) = psi^a_p(z_i), D(i, p) = d psi^a_p / dz (z_i)
 template <int P, class T>
