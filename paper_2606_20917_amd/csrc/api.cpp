@@ -124,13 +124,13 @@ static int resolve_variant(int shape, int P, int dtype, int deformed = 1) {
 // blocks, of 16 elements and more, each with the whole of a long GEMM to run, so a small batch waits
 // for one block: 56 us for 64 to 4,000 tetrahedra at P = 10, where the groups of the pencil kernel
 // take 21 us a round of 1,280 elements.  Below these counts the pencil kernel was the faster one
-// (MI355X, 64 to 40,000 elements, matrix cores -> pencil, us): tetrahedra at 1,000 elements 20.5 ->
-// 13.4, 28.3 -> 16.9, 88.8 -> 19.3 and 56.5 -> 21.6 at P = 7..10 in FP64, 19.3 -> 10.0, 23.8 -> 11.2,
-// 50.6 -> 14.0 and 58.0 -> 16.0 in FP32 (at 8,000 elements 21.2 -> 47.2 and 24.5 -> 36.8 at P = 7 in
-// FP64 and P = 8 in FP32); pyramids at 1,000 elements 21.6 -> 10.7 (P = 5) and 44.8 -> 12.2 (P = 6);
+// (MI355X, 64 to 40,000 elements, matrix cores -> pencil, us): tetrahedra at 1,000 elements 17.4 ->
+// 13.0, 28.3 -> 16.9, 77.6 -> 18.9 and 56.5 -> 21.6 at P = 7..10 in FP64, 23.8 -> 11.2, 50.6 -> 13.3
+// and 58.0 -> 16.0 at P = 8..10 in FP32, at P = 7 9.1 -> 10.0 (at 8,000 elements 18.1 -> 45.6 and 24.5
+// -> 36.8 at P = 7 in FP64 and P = 8 in FP32); pyramids at 1,000 elements 21.6 -> 10.7 (P = 5) and 44.8 -> 12.2 (P = 6);
 // prisms at P = 4 at every count (40,000: 31.6 -> 30.8, in FP32 21.4 -> 17.0)
 static int64_t dense_from(int shape, int P, int dtype) {
-  static constexpr int64_t tet[2][4] = {{4096, 4096, 4096, 3840}, {2048, 1792, 6144, 2560}};   // FP32, FP64; P = 7..10
+  static constexpr int64_t tet[2][4] = {{0, 4096, 6144, 3840}, {2048, 1792, 6144, 2560}};   // FP32, FP64; P = 7..10
   const int f64 = dtype == NIR_F64;
   if (shape == kTet) return P >= 7 ? tet[f64][P - 7] : 0;
   if (shape == kPyr && P >= 5) return P == 5 && f64 ? 4096 : 8192;

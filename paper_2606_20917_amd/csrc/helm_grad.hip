@@ -212,13 +212,15 @@ __global__ void __launch_bounds__(64 * NW) k_helm_grad(const T* __restrict__ B1,
     }
 }
 
-// Block shape by order and type: the fastest of NW in {4, 8}, WC, RTW in 1..4 and PD in {1, 2} on
-// 82,944 and 9,001 affine tetrahedra (MI355X, lambda = 1).  At P <= 4 one or two column tiles hold
-// everything and the wavefronts split the rows; from P = 5 they split the columns, so that each B
-// operand is read by one wavefront only; from P = 7 a block has 8 wavefronts, two per SIMD, as T of
-// its rows leaves LDS for one or two blocks a CU.  Time in us on 82,944 elements, seven stacked
-// reference matrices -> this kernel, P = 4..10:
-//   FP64   24.2 -> 17.8   53.9 -> 40.6   97 -> 76   190 -> 186   385 -> 272   955 -> 672  1353 -> 1057
+// Block shape by order and type: the fastest of NW in {4, 6, 8, 12, 16}, WC, RTW in 1..4 and PD in
+// {1, 2} on 82,944 and 9,001 affine tetrahedra (MI355X, lambda = 1).  At P <= 4 one or two column tiles
+// hold everything and the wavefronts split the rows; from P = 5 they split the columns, so that each B
+// operand is read by one wavefront only, in a count that the tiles of both GEMMs divide: at P = 7 11
+// and 6 tiles by 6 wavefronts (FP64, by 4: 184 -> 156 us; FP32 at 9,001 elements 20.1 -> 16.7), at P = 9
+// 23 and 11 by 12 (by 8: 670 -> 584).  From P = 8 a block has 8 wavefronts and more, as T of its rows
+// leaves LDS for one or two blocks a CU.  Time in us on 82,944 elements, seven stacked reference
+// matrices -> this kernel, P = 4..10:
+//   FP64   24.2 -> 17.8   53.9 -> 40.6   97 -> 76   190 -> 156   385 -> 272   955 -> 584  1353 -> 1057
 //   FP32   13.7 -> 10.2   37.8 -> 22.8   53 -> 44   125 -> 95    185 -> 148   480 -> 302   651 -> 568
 struct GradCfg {
   int NW, WC, RTW, PD;
@@ -226,9 +228,9 @@ struct GradCfg {
 template <int P, class T>
 constexpr GradCfg grad_cfg() {
   constexpr GradCfg c64[9] = {{4, 1, 1, 2}, {4, 1, 1, 1}, {4, 2, 1, 2}, {4, 4, 1, 2}, {4, 4, 1, 2},
-                              {8, 4, 1, 2}, {8, 8, 2, 2}, {8, 8, 3, 2}, {8, 8, 1, 1}};
+                              {12, 6, 1, 1}, {8, 8, 2, 2}, {12, 12, 3, 2}, {8, 8, 1, 1}};
   constexpr GradCfg c32[9] = {{4, 1, 1, 2}, {4, 1, 2, 1}, {4, 1, 1, 2}, {4, 4, 2, 2}, {4, 4, 1, 2},
-                              {4, 4, 3, 1}, {8, 8, 3, 2}, {4, 4, 3, 1}, {8, 8, 2, 1}};
+                              {6, 6, 1, 1}, {8, 8, 3, 2}, {4, 4, 3, 1}, {8, 8, 2, 1}};
   return sizeof(T) == 8 ? c64[P - 2] : c32[P - 2];
 }
 

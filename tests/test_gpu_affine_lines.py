@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 F32, F64 = nir.F32, nir.F64
 LINES = [(nir.TET, 6, F64, 0), (nir.TET, 7, F64, 2048), (nir.TET, 8, F64, 1792), (nir.TET, 9, F64, 6144),
-         (nir.TET, 10, F64, 2560), (nir.TET, 7, F32, 4096), (nir.TET, 8, F32, 4096), (nir.TET, 9, F32, 4096),
+         (nir.TET, 10, F64, 2560), (nir.TET, 7, F32, 0), (nir.TET, 8, F32, 4096), (nir.TET, 9, F32, 6144),
          (nir.TET, 10, F32, 3840), (nir.PYR, 4, F64, 0), (nir.PYR, 5, F64, 4096), (nir.PYR, 6, F64, 8192),
          (nir.PYR, 5, F32, 8192), (nir.PYR, 6, F32, 8192), (nir.PRISM, 3, F32, 0), (nir.PRISM, 4, F64, None),
          (nir.PRISM, 4, F32, None)]
