@@ -94,9 +94,7 @@ static nir_status native_only(const nir_batch* b) {
 // variant table [shape][P][dtype]; 0 = auto
 static std::atomic<int> g_variant[4][kMaxP + 1][2];
 
-static int resolve_variant(int shape, int P, int dtype, int deformed = 1) {
-  const int v = g_variant[shape][P][dtype].load(std::memory_order_relaxed);
-  if (v != NIR_VARIANT_AUTO) return v;
+static int default_variant(int shape, int P, int dtype, int deformed) {
   // the matrix cores for affine batches of a size (dense_from; the pencil kernel runs the others):
   // tetrahedra at every order, in the gradient form (40,000 at P = 10 in FP64: 491 us, the pencil
   // kernel 629), prisms to P = 4 and pyramids to P = 6, past which the pencil kernel is faster
@@ -137,23 +135,25 @@ static int64_t dense_from(int shape, int P, int dtype) {
   return shape == kPrism && P == 4 ? std::numeric_limits<int64_t>::max() : 0;
 }
 
-// whether launch_helm_auto takes gathered coefficients (OpArgs::map) for this basis now: the hex
-// pencil kernels do, the generic one does not
-bool helm_gathers(const nir_basis* basis, int dtype) {
-  return basis->shape == kHex && resolve_variant(kHex, basis->P, dtype) != NIR_VARIANT_GENERIC;
+int helm_variant(int shape, int P, int dtype, int deformed, int64_t nelmt) {
+  int v = g_variant[shape][P][dtype].load(std::memory_order_relaxed);
+  if (v == NIR_VARIANT_AUTO) {
+    v = default_variant(shape, P, dtype, deformed);
+    if (v == NIR_VARIANT_DENSE && nelmt < dense_from(shape, P, dtype)) v = NIR_VARIANT_PENCIL;
+  }
+  // per-point factors or M > kDenseMaxM: the register-pencil kernel
+  if (v == NIR_VARIANT_DENSE && (deformed || modes_of(shape, P) > kDenseMaxM)) v = NIR_VARIANT_PENCIL;
+  return v;
 }
 
-// the fused Helmholtz apply with the selected kernel variant (native contractions)
-nir_status launch_helm_auto(const nir_basis* basis, int dtype, int deformed, const OpArgs& a, hipStream_t s) {
-  int v = resolve_variant(basis->shape, basis->P, dtype, deformed);
-  const bool by_default =
-      g_variant[basis->shape][basis->P][dtype].load(std::memory_order_relaxed) == NIR_VARIANT_AUTO;
-  if (v == NIR_VARIANT_DENSE && by_default && a.nelmt < dense_from(basis->shape, basis->P, dtype)) v = NIR_VARIANT_PENCIL;
-  if (v == NIR_VARIANT_DENSE) {
-    if (basis->shape == kTet && !deformed && basis->grad64) return launch_helm_grad(basis, dtype, a, s);
-    if (basis->shape != kHex && !deformed && basis->dense64) return launch_helm_dense(basis, dtype, a, s);
-    v = NIR_VARIANT_PENCIL;   // per-point factors or M > kDenseMaxM: the register-pencil kernel
-  }
+// the hex pencil kernels gather, the generic one and the collapsed shapes' do not
+bool helm_gathers(int shape, int variant) { return shape == kHex && variant != NIR_VARIANT_GENERIC; }
+
+nir_status launch_helm_variant(int v, const nir_basis* basis, int dtype, int deformed, const OpArgs& a, hipStream_t s) {
+  if (a.map && !helm_gathers(basis->shape, v))
+    return fail(NIR_EINVAL, "variant %d takes no gathered coefficients", v);
+  if (v == NIR_VARIANT_DENSE)
+    return basis->shape == kTet ? launch_helm_grad(basis, dtype, a, s) : launch_helm_dense(basis, dtype, a, s);
   if (basis->shape == kPrism && v == NIR_VARIANT_PENCIL) return launch_helm_col_prism(basis, dtype, deformed, a, s);
   if (basis->shape == kTet && v == NIR_VARIANT_PENCIL) return launch_helm_col_tet(basis, dtype, deformed, a, s);
   if (basis->shape == kPyr && v == NIR_VARIANT_PENCIL) return launch_helm_col_pyr(basis, dtype, deformed, a, s);
@@ -168,6 +168,10 @@ nir_status launch_helm_auto(const nir_basis* basis, int dtype, int deformed, con
   if (v == NIR_VARIANT_PENCIL_EO) return launch_helm_hex_eo(basis, dtype, deformed, a, s, false);
   if (v == NIR_VARIANT_PENCIL_EO_SPLIT) return launch_helm_hex_eo(basis, dtype, deformed, a, s, true);
   return launch_generic(basis, kOpHelm, dtype, deformed, a, s);
+}
+
+nir_status launch_helm_auto(const nir_basis* basis, int dtype, int deformed, const OpArgs& a, hipStream_t s) {
+  return launch_helm_variant(helm_variant(basis->shape, basis->P, dtype, deformed, a.nelmt), basis, dtype, deformed, a, s);
 }
 
 }  // namespace nir
@@ -855,7 +859,8 @@ nir_status nir_set_helmholtz_variant(int32_t shape, int32_t P, int32_t dtype, in
 
 int32_t nir_get_helmholtz_variant(int32_t shape, int32_t P, int32_t dtype) {
   if (shape < kHex || shape > kPyr || P < kMinP || P > kMaxP || (dtype != NIR_F64 && dtype != NIR_F32)) return -1;
-  return resolve_variant(shape, P, dtype);
+  const int v = g_variant[shape][P][dtype].load(std::memory_order_relaxed);
+  return v != NIR_VARIANT_AUTO ? v : default_variant(shape, P, dtype, 1);
 }
 
 }  // extern "C"

@@ -424,7 +424,9 @@ namespace nir {
 // (57 MB written and read again) and a launch become 6 us of the apply (74.9 -> 80.9 us)
 static nir_status apply_elements(nir_cg_plan* pl, int dtype, hipStream_t s, const void* xg) {
   const nir_assembly* A = pl->A;
-  const bool own = helm_gathers(pl->basis, dtype) && !(dtype == NIR_F32 && pl->f16split);
+  // the variant is asked for once: the vector handed over has to fit the kernel that runs
+  const int variant = helm_variant(pl->basis->shape, pl->basis->P, dtype, pl->b64.deformed, pl->b64.nelmt);
+  const bool own = helm_gathers(pl->basis->shape, variant) && !(dtype == NIR_F32 && pl->f16split);
   OpArgs a{};
   a.lambda = pl->lambda;
   a.nelmt = pl->b64.nelmt;
@@ -439,7 +441,7 @@ static nir_status apply_elements(nir_cg_plan* pl, int dtype, hipStream_t s, cons
     }
     a.out0 = pl->yl;
     a.helm = pl->g64.helm;
-    NIR_TRYS(launch_helm_auto(pl->basis, NIR_F64, pl->b64.deformed, a, s));
+    NIR_TRYS(launch_helm_variant(variant, pl->basis, NIR_F64, pl->b64.deformed, a, s));
   } else {
     if (own) {
       a.in0 = xg;
@@ -454,7 +456,7 @@ static nir_status apply_elements(nir_cg_plan* pl, int dtype, hipStream_t s, cons
     if (pl->f16split)
       NIR_TRYS(launch_helm_hex_f16split(pl->basis, pl->b64.deformed, a, s));
     else
-      NIR_TRYS(launch_helm_auto(pl->basis, NIR_F32, pl->b64.deformed, a, s));
+      NIR_TRYS(launch_helm_variant(variant, pl->basis, NIR_F32, pl->b64.deformed, a, s));
   }
   return hip_check(hipGetLastError(), "assembled apply launch");
 }

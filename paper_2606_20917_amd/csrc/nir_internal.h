@@ -249,8 +249,16 @@ nir_status build_dense_refs(nir_basis* b);
 // build_grad_tables places in the basis
 nir_status launch_helm_grad(const nir_basis* b, int dtype, const OpArgs& a, hipStream_t s);
 nir_status build_grad_tables(nir_basis* b);
-// the fused Helmholtz apply with the currently selected kernel variant (native contractions)
-bool helm_gathers(const nir_basis* basis, int dtype);
+// The fused Helmholtz apply (native contractions).  helm_variant: the variant that a call with these
+// parameters runs now (never NIR_VARIANT_AUTO).  The selection is one load, and another thread may
+// change it at any time: a caller whose arguments depend on the variant asks once, prepares them and
+// hands that variant to launch_helm_variant.  helm_gathers: whether a variant takes gathered
+// coefficients (OpArgs::map); the launch refuses a map where it does not.
+int helm_variant(int shape, int P, int dtype, int deformed, int64_t nelmt);
+bool helm_gathers(int shape, int variant);
+nir_status launch_helm_variant(int variant, const nir_basis* basis, int dtype, int deformed, const OpArgs& a,
+                               hipStream_t s);
+// the two in one: the apply with the variant selected now
 nir_status launch_helm_auto(const nir_basis* basis, int dtype, int deformed, const OpArgs& a, hipStream_t s);
 nir_status launch_points(const nir_basis* b, int64_t nelmt, const double* verts, double amp, double* xyz,
                          hipStream_t s);
