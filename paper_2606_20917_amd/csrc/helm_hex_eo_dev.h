@@ -90,7 +90,9 @@ __device__ __forceinline__ void helm_hex_eo_group(const T* __restrict__ tabs, co
   if constexpr (SF) {
     // the coefficients, then the block's factors, with buffer loads and no branch (reads past a
     // descriptor's size return zeros), so that each wait counts exactly the requests it needs:
-    // the coefficients are requested first because the vector memory counter completes in order
+    // the coefficients are requested first because the vector memory counter completes in order.
+    // The whole offset is the lane's: a scalar offset is left out of the range check, or taken from
+    // the records, of which a short last group has fewer
     const __amdgpu_buffer_rsrc_t frs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<T*>(helm + base * NF7), short(0), (ne > 0 ? ne : 0) * NF7 * int(sizeof(T)), 0x00020000);
     T xv[PERX];
@@ -99,18 +101,18 @@ __device__ __forceinline__ void helm_hex_eo_group(const T* __restrict__ tabs, co
           const_cast<int32_t*>(map + base * M), short(0), (ne > 0 ? ne : 0) * M * 4, 0x00020000);
       int32_t gi[PERX];
 #pragma unroll
-      for (int k = 0; k < PERX; ++k) gi[k] = buf_load<int32_t>(mrs, t * 4, k * BLOCK * 4);
+      for (int k = 0; k < PERX; ++k) gi[k] = buf_load<int32_t>(mrs, (t + k * BLOCK) * 4, 0);
 #pragma unroll
       for (int k = 0; k < PERX; ++k) xv[k] = x[gi[k]];
     } else {
       const __amdgpu_buffer_rsrc_t xrs = __builtin_amdgcn_make_buffer_rsrc(
           const_cast<T*>(x + base * M), short(0), (ne > 0 ? ne : 0) * M * int(sizeof(T)), 0x00020000);
 #pragma unroll
-      for (int k = 0; k < PERX; ++k) xv[k] = buf_load<T>(xrs, t * int(sizeof(T)), k * BLOCK * int(sizeof(T)));
+      for (int k = 0; k < PERX; ++k) xv[k] = buf_load<T>(xrs, (t + k * BLOCK) * int(sizeof(T)), 0);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int k = 0; k < PERF; ++k) fv[k] = buf_load<T>(frs, t * int(sizeof(T)), k * BLOCK * int(sizeof(T)));
+    for (int k = 0; k < PERF; ++k) fv[k] = buf_load<T>(frs, (t + k * BLOCK) * int(sizeof(T)), 0);
     // unconditional stores (threads past the group's coefficients write the junk row), so that no
     // coefficient load is sunk into a branch behind the factors' requests
 #pragma unroll

@@ -44,7 +44,8 @@ template <int P, class T>
 struct HexTabC;
 
 // raw buffer load of one value at byte offset voff (per lane) + soff (uniform); reads past the
-// descriptor's size return zero
+// descriptor's size return zero as far as voff takes them there: soff must not pass the size, and
+// voff by itself must reach it for the lanes that have nothing to read
 template <class T>
 __device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
   if constexpr (sizeof(T) == 8)
