@@ -32,7 +32,7 @@ using std::min;
 struct HostLane {
   unsigned x;
 };
-inline thread_local HostLane threadIdx{0};
+inline thread_local HostLane threadIdx{0}, blockIdx{0}, gridDim{1};
 inline pthread_barrier_t host_barrier;
 inline void __syncthreads() { pthread_barrier_wait(&host_barrier); }
 
@@ -109,6 +109,11 @@ inline void run_blocks(int threads, int64_t nblocks, const std::function<void(in
   pthread_barrier_destroy(&host_barrier);
 }
 
-// register fences: `asm volatile("" : ...)` in the device headers below
+// What only the device compiler understands in the headers that follow: register fences
+// (`asm volatile("" : ...)`), address spaces, launch bounds, register budgets, kernel launches
 #define asm
 #define volatile(...)
+#define __attribute__(...)
+#define __launch_bounds__(...)
+#undef hipLaunchKernelGGL
+#define hipLaunchKernelGGL(...)

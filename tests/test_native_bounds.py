@@ -1,6 +1,8 @@
-"""Device functions of one block on the host, one thread per lane, under AddressSanitizer and
-UndefinedBehaviorSanitizer (tests/native/host_lanes.h): every buffer in an allocation of its exact size,
-buffer loads checked against both readings of the hardware's range check.  Host code only."""
+"""Device functions of one block on the host, one thread per lane, under AddressSanitizer,
+UndefinedBehaviorSanitizer or ThreadSanitizer (tests/native/host_lanes.h): every buffer in an allocation
+of its exact size, buffer loads checked against both readings of the hardware's range check, and no two
+lanes at one value without a barrier between.  Host code only."""
+import concurrent.futures as cf
 import os
 import shutil
 import subprocess
@@ -15,11 +17,14 @@ pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir
                                 reason="needs g++ and the HIP headers")
 
 
-def _run(tmp_path, name, *flags):
-    exe = str(tmp_path / name)
-    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
-           "-fno-omit-frame-pointer", "-w", "-D__HIP_PLATFORM_AMD__", *flags, "-I" + ROCM_INC, "-I" + CSRC,
-           os.path.join(ROOT, "tests", "native", name + ".cpp"), "-o", exe, "-lpthread"]
+SANITIZERS = "address,undefined"
+
+
+def _run(tmp_path, name, sanitize=SANITIZERS, sources=(), flags=("-O1", "-g")):
+    exe = str(tmp_path / (name + "_".join(("", *flags, sanitize)).replace(",", "_")))
+    cmd = ["g++", "-std=c++17", "-fsanitize=" + sanitize, "-fno-sanitize-recover=all", "-fno-omit-frame-pointer", "-w",
+           "-D__HIP_PLATFORM_AMD__", *flags, "-I" + ROCM_INC, "-I" + CSRC,
+           os.path.join(ROOT, "tests", "native", name + ".cpp"), *sources, "-o", exe, "-lpthread"]
     r = subprocess.run(cmd, capture_output=True, text=True, timeout=900)
     assert r.returncode == 0, r.stderr[-4000:]
     # verify_asan_link_order=0: a library the environment preloads may come before the ASan runtime
@@ -31,3 +36,20 @@ def _run(tmp_path, name, *flags):
 
 def test_staged_hexahedral_groups_stay_in_bounds(tmp_path):
     _run(tmp_path, "hex_staged_bounds")
+
+
+@pytest.mark.parametrize("shape", [1, 2, 3], ids=["prism", "tet", "pyr"])
+def test_collapsed_groups_stay_in_bounds(shape, tmp_path):
+    """Every order under AddressSanitizer, two of them under ThreadSanitizer."""
+    sources = [os.path.join(CSRC, f) for f in ("api.cpp", "tables.cpp")]
+
+    def one(job):
+        P, sanitize = job
+        # api.cpp makes the tables; the launches that it refers to are not linked in and not called
+        flags = ("-O0", "-fpermissive", "-Wl,--unresolved-symbols=ignore-all", f"-DCHECK_SHAPE={shape}",
+                 f"-DCHECK_PMIN={P}", f"-DCHECK_PMAX={P}")
+        _run(tmp_path, "col_bounds", sanitize, sources, flags)
+
+    jobs = [(P, "address") for P in range(10, 1, -1)] + [(P, "thread") for P in (6, 3)]
+    with cf.ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as ex:
+        list(ex.map(one, jobs))
