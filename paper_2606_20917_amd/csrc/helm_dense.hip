@@ -28,6 +28,7 @@
 #include <vector>
 
 #include "generic_ops.h"
+#include "half_bits.h"
 #include "mfma_tile.h"
 #include "nir_internal.h"
 
@@ -369,7 +370,9 @@ nir_status launch_helm_dense_f16split(const nir_basis* b, const OpArgs& a, hipSt
 // The seven reference matrices of (shape, P), stacked [7 MP][MP] and zero-padded, in FP64 and an
 // FP32 copy: the generic Helmholtz kernel applied (lambda = 1, per-element factors) to 7 M unit
 // "elements", element (c, m) holding x = e_m and the factors g = e_c, gives row m of matrix c
-// (the matrices are symmetric).  Synchronous; the basis owns dense64 afterwards, which holds dense32 and dense16 too.
+// (the matrices are symmetric).  Tetrahedra keep the last of them alone, the mass matrix, in FP64 and
+// FP32 (helm_grad.hip), and all seven in FP16.  Synchronous; the basis owns dense64 afterwards, which
+// holds dense32 and dense16 too.
 nir_status build_dense_refs(nir_basis* b) {
   const int M = b->M, MP = (M + 15) / 16 * 16;
   if (M > kDenseMaxM) return NIR_OK;   // the sum-factorised kernels only
@@ -398,16 +401,18 @@ nir_status build_dense_refs(nir_basis* b) {
   (void)hipFree(dx);
   if (st != NIR_OK) return st;
   // one array: FP64, FP32, FP16 hi and lo (MP^2 is a multiple of 256, so each part is aligned)
-  const size_t half = size_t(7) * MP * MP;
-  std::vector<double> all(2 * half, 0.0);
+  const int c0 = b->shape == kTet ? 6 : 0;   // the first matrix kept in FP64 and FP32
+  const size_t sq = size_t(MP) * MP, part = (7 - c0) * sq, half = 7 * sq;
+  std::vector<double> all((12 * part + 4 * half) / 8, 0.0);
   double* s64 = all.data();
-  float* s32 = reinterpret_cast<float*>(s64 + half);
-  _Float16* s16 = reinterpret_cast<_Float16*>(s32 + half);
-  for (int c = 0; c < 7; ++c)
+  float* s32 = reinterpret_cast<float*>(s64 + part);
+  uint16_t* s16 = reinterpret_cast<uint16_t*>(s32 + part);
+  auto ref = [&](int c, int m, int n) { return hy[(size_t(c) * M + m) * M + n]; };
+  for (int c = c0; c < 7; ++c)
     for (int m = 0; m < M; ++m)
       for (int n = 0; n < M; ++n) {
-        const size_t o = (size_t(c) * MP + m) * MP + n;
-        s64[o] = hy[(size_t(c) * M + m) * M + n];
+        const size_t o = (c - c0) * sq + size_t(m) * MP + n;
+        s64[o] = ref(c, m, n);
         s32[o] = float(s64[o]);
       }
   // FP16-split copies for v_mfma_f32_16x16x16f16: sigma_c S_c in [1/2, 1) split into hi and lo
@@ -416,8 +421,7 @@ nir_status build_dense_refs(nir_basis* b) {
   const int NKB = MP / 16, NCT = MP / 16;
   for (int c = 0; c < 7; ++c) {
     double mx = 0.0;
-    for (int m = 0; m < M; ++m)
-      for (int n = 0; n < M; ++n) mx = std::max(mx, std::fabs(s64[(size_t(c) * MP + m) * MP + n]));
+    for (size_t k = size_t(c) * M * M; k < size_t(c + 1) * M * M; ++k) mx = std::max(mx, std::fabs(hy[k]));
     int ex = 0;
     if (mx > 0.0) std::frexp(mx, &ex);
     const double sig = std::ldexp(1.0, -ex);
@@ -427,16 +431,17 @@ nir_status build_dense_refs(nir_basis* b) {
         for (int l = 0; l < 64; ++l)
           for (int v = 0; v < 4; ++v) {
             const int k = kb * 16 + 4 * (l / 16) + v, j = ct * 16 + l % 16;
-            const float a = float(sig * s64[(size_t(c) * MP + k) * MP + j]);
-            const _Float16 hi = (_Float16)a;
+            if (k >= M || j >= M) continue;
+            const float a = float(sig * ref(c, k, j));
             const size_t o = ((size_t(c * NKB + kb) * NCT + ct) * 64 + l) * 4 + v;
-            s16[o] = hi;
-            s16[half + o] = (_Float16)((a - float(hi)) * 2048.f);
+            float hi, lo;
+            s16[o] = half_bits(a, &hi);
+            s16[half + o] = half_bits((a - hi) * 2048.f, &lo);
           }
   }
   NIR_TRYS(hip_check(hipMalloc(&b->dense64, all.size() * 8), "hipMalloc"));
-  b->dense32 = reinterpret_cast<float*>(b->dense64 + half);
-  b->dense16 = b->dense32 + half;
+  b->dense32 = reinterpret_cast<float*>(b->dense64 + part);
+  b->dense16 = b->dense32 + part;
   return hip_check(hipMemcpy(b->dense64, all.data(), all.size() * 8, hipMemcpyHostToDevice), "copy");
 }
 

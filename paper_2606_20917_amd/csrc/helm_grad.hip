@@ -251,7 +251,7 @@ static nir_status launch_grad_P(const nir_basis* b, const OpArgs& a, hipStream_t
     Mm = b->dense32;
   }
   hipLaunchKernelGGL((k_helm_grad<P, T, c.NW, c.WC, c.RTW, c.PD>), dim3(unsigned(nb)), dim3(D::BLOCK), 0, s, B1,
-                     Mm + 6 * D::MP * D::MP, B1 + D::MK * D::N1P, static_cast<const T*>(a.in0),
+                     Mm, B1 + D::MK * D::N1P, static_cast<const T*>(a.in0),
                      static_cast<T*>(a.out0), static_cast<const T*>(a.helm), T(a.lambda), a.nelmt);
   return hip_check(hipGetLastError(), "affine tetrahedron Helmholtz launch");
 }

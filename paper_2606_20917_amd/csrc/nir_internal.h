@@ -143,11 +143,11 @@ struct nir_basis {
   float* mfma_tabs = nullptr;
   float* mfma_scale = nullptr;
   // collapsed shapes: the seven reference matrices of the affine Helmholtz operator, stacked
-  // [7 MP][MP] (MP = M rounded up to 16), FP64 and an FP32 copy (helm_dense.hip); dense32 and
-  // dense16 lie in the same array
+  // [7 MP][MP] (MP = M rounded up to 16; tetrahedra: the last one alone, the mass matrix), FP64 and an
+  // FP32 copy (helm_dense.hip); dense32 and dense16 lie in the same array
   double* dense64 = nullptr;
   float* dense32 = nullptr;
-  // the same, scaled per matrix by sigma_c into [1/2, 1) and split into FP16 hi and lo parts packed
+  // all seven, scaled per matrix by sigma_c into [1/2, 1) and split into FP16 hi and lo parts packed
   // in the B layout of v_mfma_f32_16x16x16f16 (hi block, then lo block), and the 1 / sigma_c
   void* dense16 = nullptr;
   float dense_inv[7] = {1, 1, 1, 1, 1, 1, 1};

@@ -34,6 +34,10 @@ def _run(tmp_path, name, sanitize=SANITIZERS, sources=(), flags=("-O1", "-g")):
     assert " 0 failures" in r.stdout
 
 
+def test_half_conversion_rounds_to_nearest_even(tmp_path):
+    _run(tmp_path, "half_bits", flags=("-O2",))
+
+
 def test_staged_hexahedral_groups_stay_in_bounds(tmp_path):
     _run(tmp_path, "hex_staged_bounds")
 
