@@ -191,6 +191,20 @@ constexpr bool col_early() {
   return DEF && P > 2;
 }
 
+// Chain-rule factors of a point pencil (eq. (23)): d eta1 / d xi1 = 2 k1 and, with z1 = 1 + eta1,
+// d eta1 / d xi3 = k1 z1 (tet: / d xi2 too); with e2 = 1 + eta2, d eta2 / d xi2 = 2 k2 and
+// d eta2 / d xi3 = k2 e2 (tet and pyramid; 1 and 0 for the prism).  k1 divides by 1 - eta2 as it is, not by
+// 2 - e2: near the collapsed edge the rounding of e2 is several ulps of the difference.
+template <class T>
+struct ColChain {
+  T e2, k1, k2;
+};
+template <int SHAPE, class T>
+__host__ __device__ __forceinline__ ColChain<T> col_chain(T z2, T z3) {
+  const T r3 = T(1) / (T(1) - z3);
+  return {T(1) + z2, SHAPE == kTet ? T(2) * r3 / (T(1) - z2) : r3, r3};
+}
+
 // OPM = 1: the backward transform only (u = B c at the points, into y[nelmt][Q^3]): the value
 // halves of A and B, then C without the pointwise step; helm and lambda are not used.
 // OPM = 2: the inner product with the basis only (y = B^T W u for u = x[nelmt][Q^3], W = w |J|
@@ -688,11 +702,8 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
   // ---- C, pointwise, C^T fused over the (j,k) pencils, streamed over the points i or the point pairs
   // (i, Q-1-i) (the wavefronts without pencils go straight to the barrier)
   if constexpr (!NOFWD) {
-    // chain-rule factors of the pencil (eq. (23)): d eta1 / d xi1 = 2 k1 and, with z1 = 1 + eta1,
-    // d eta1 / d xi3 = k1 z1 (tet: / d xi2 too); d eta2 / d xi2 = 2 k2 and d eta2 / d xi3 = k2 e2
-    // (tet and pyramid; 1 and 0 for the prism)
-    const T e2 = T(1) + tb.z[1][act ? jj : 0], r3 = T(1) / (T(1) - tb.z[2][act ? kk : 0]);
-    const T k1 = TET ? T(2) * r3 / (T(2) - e2) : r3, k2 = r3;
+    const ColChain<T> ch = col_chain<SHAPE>(tb.z[1][act ? jj : 0], tb.z[2][act ? kk : 0]);
+    const T e2 = ch.e2, k1 = ch.k1, k2 = ch.k2;
     const int vk = 1 * Q + (act ? kk : 0);   // the vertex mode (0,0,1) in T3, dT3
     const T uv = VTX ? c001 * tb.T3[vk] : T(0), dv = VTX ? c001 * tb.dT3[vk] : T(0);
     T vm = T(0), v3 = T(0);

@@ -57,3 +57,7 @@ def test_collapsed_groups_stay_in_bounds(shape, tmp_path):
     jobs = [(P, "address") for P in range(10, 1, -1)] + [(P, "thread") for P in (6, 3)]
     with cf.ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as ex:
         list(ex.map(one, jobs))
+
+
+def test_chain_factors_of_collapsed_points(tmp_path):
+    _run(tmp_path, "col_chain", sources=[os.path.join(CSRC, "tables.cpp")])
