@@ -271,10 +271,10 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
   // lanes past the last element read past the descriptor's size and get zeros.  The first pair's are
   // requested here and stay in flight through sweeps A and B (barriers do not wait for loads).
   // Affine elements request the points' weights instead.
-  // A group past the batch's end requests nothing: its descriptor has no records, and the scalar
-  // offsets would pass them.
+  // A group past the batch's end (one of several in a block; a block has an element) requests nothing:
+  // its descriptor has no records, and the scalar offsets would pass them.
   constexpr bool HELM = !BWD && !NOFWD;
-  const bool pencils = ne > 0 && wave < D::NWP;
+  const bool pencils = in && (NSUB == 1 || ne > 0) && wave < D::NWP;
   // The descriptor must sit in SGPRs: in a function that is not inlined (the mixed kernel's items) its
   // parts arrive in VGPRs, and every load through it would loop over the lanes' descriptors (20,000
   // tetrahedra in FP32 in the persistent kernel, P = 5 59.4 -> 52.2 us, P = 8 199 -> 187 us).
