@@ -16,12 +16,12 @@
 
 #include "helm_hex.h"
 #include "nir_internal.h"
+#include "row_sum.h"
 
 namespace nir {
 
 constexpr int kRedBlocks = 1024;   // partial sums per reduction (fixed: deterministic order)
 constexpr int kRedThreads = 256;
-constexpr int kScatterEntries = 4;   // entries of a scatter-reduce row read together
 
 // ---------------------------------------------------------------- C0 map
 __host__ __device__ inline int64_t c0_g1(int64_t i, int p, int P) {
@@ -44,29 +44,6 @@ template <class T>
 __global__ void k_gather(const int32_t* __restrict__ l2g, const T* __restrict__ xg, T* __restrict__ xl, int64_t n) {
   for (int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; t < n; t += int64_t(gridDim.x) * blockDim.x)
     xl[t] = xg[l2g[t]];
-}
-
-// Sum of CSR row g over its entries in ascending (element, mode) order.  A row is a chain of
-// dependent reads (offsets, index, value) and holds one to eight entries on a mesh of hexahedra, so
-// K entries go through every stage together: three memory latencies for a row of up to K.
-template <class T>
-__device__ __forceinline__ T row_sum(const int32_t* __restrict__ off, const int32_t* __restrict__ idx,
-                                     const T* __restrict__ yl, int64_t g) {
-  constexpr int K = kScatterEntries;
-  const int32_t at = off[g], end = off[g + 1];
-  T s = T(0);
-  for (int32_t k = at; k < end; k += K) {
-    int32_t n[K];
-    T v[K];
-#pragma unroll
-    for (int i = 0; i < K; ++i) n[i] = k + i < end ? idx[k + i] : -1;
-#pragma unroll
-    for (int i = 0; i < K; ++i) v[i] = n[i] >= 0 ? yl[n[i]] : T(0);
-#pragma unroll
-    for (int i = 0; i < K; ++i)
-      if (n[i] >= 0) s += v[i];
-  }
-  return s;
 }
 
 // The dispatcher deals blocks to the 8 XCDs in turn; block b takes the work of block xcd_block(b), so

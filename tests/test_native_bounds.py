@@ -61,3 +61,7 @@ def test_collapsed_groups_stay_in_bounds(shape, tmp_path):
 
 def test_chain_factors_of_collapsed_points(tmp_path):
     _run(tmp_path, "col_chain", sources=[os.path.join(CSRC, "tables.cpp")])
+
+
+def test_rows_at_the_end_of_the_index_range(tmp_path):
+    _run(tmp_path, "row_sum_edges")
