@@ -210,6 +210,15 @@ def _stream(stream):
     return s
 
 
+def _forget_stream_getters():
+    """In a forked child: torch refuses the GPU there, so its first call goes through torch again."""
+    global _current
+    _current = None
+
+
+os.register_at_fork(after_in_child=_forget_stream_getters)
+
+
 def batch(shape, P, nelmt, dtype=F64, deformed=1, math=MATH_NATIVE, Q=None):
     return nir_batch(shape, P, P + 1 if Q is None else Q, deformed, nelmt, dtype, math)
 
