@@ -428,6 +428,10 @@ nir_status nir_set_helmholtz_variant(int32_t shape, int32_t P, int32_t dtype, in
 /* The variant a call with these parameters and per-point factors would run now (never NIR_VARIANT_AUTO;
  * NIR_VARIANT_DENSE stands for the choice it makes); -1 if invalid. */
 int32_t nir_get_helmholtz_variant(int32_t shape, int32_t P, int32_t dtype);
+/* The variant that nir_helmholtz_apply would run now on this batch: its factors (deformed) and its
+ * element count decide between the built-in choices, and NIR_VARIANT_DENSE is answered only where
+ * that kernel runs.  -1 if the batch is invalid or asks for other than native math. */
+int32_t nir_get_helmholtz_variant_of(const nir_batch* batch);
 /* Autotuner: times every variant applicable to the batch's shape on the caller's operands
  * (one warm-up and `reps` timed applies each, hipEvents on `stream`; coef_out is overwritten),
  * selects the fastest for (shape, P, dtype) and returns it in *chosen.  ms_per_variant, if not

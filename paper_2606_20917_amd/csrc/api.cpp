@@ -863,6 +863,17 @@ int32_t nir_get_helmholtz_variant(int32_t shape, int32_t P, int32_t dtype) {
   return v != NIR_VARIANT_AUTO ? v : default_variant(shape, P, dtype, 1);
 }
 
+int32_t nir_get_helmholtz_variant_of(const nir_batch* b) {
+  nir_basis any{};   // check_batch compares the batch with its basis
+  if (b) {
+    any.shape = b->shape;
+    any.P = b->nmodes;
+    any.Q = b->nquad;
+  }
+  if (check_batch(b, &any) != NIR_OK || b->math != NIR_MATH_NATIVE) return -1;
+  return helm_variant(b->shape, b->nmodes, b->dtype, b->deformed, b->nelmt);
+}
+
 }  // extern "C"
 
 namespace nir {

@@ -98,6 +98,7 @@ _SIGS = {
     "nir_mixed_plan_destroy": (_i32, [_vp]),
     "nir_mixed_helmholtz_apply_noalloc": (_i32, [_i32, _vp, _vp, _vp, _dbl, _vp, _vp, _vp]),
     "nir_get_helmholtz_variant": (_i32, [_i32, _i32, _i32]),
+    "nir_get_helmholtz_variant_of": (_i32, [ctypes.POINTER(nir_batch)]),
     "nir_autotune_helmholtz": (_i32, [ctypes.POINTER(nir_batch), _vp, ctypes.POINTER(nir_geom), _dbl, _vp, _vp, _i32,
                                       _vp, _vp, _vp]),
     "nir_autotune_save": (_i32, [ctypes.c_char_p]),
@@ -409,6 +410,11 @@ def nir_set_helmholtz_variant(shape, P, dtype, variant):
 
 def nir_get_helmholtz_variant(shape, P, dtype):
     return lib().nir_get_helmholtz_variant(shape, P, dtype)
+
+
+def nir_get_helmholtz_variant_of(b):
+    """The variant that nir_helmholtz_apply would run now on the batch b; -1 if it is invalid."""
+    return lib().nir_get_helmholtz_variant_of(ctypes.byref(b))
 
 
 def nir_points_from_vertices(b, basis, verts, map_, amp, xyz, stream=None):
