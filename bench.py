@@ -349,6 +349,18 @@ def algorithmic_flops(shape, P):
     return 4 * (M * Q + P * (P + 1) // 2 * Q * Q + P * Q ** 3) + 12 * Q ** 4 + 40 * Q ** 3
 
 
+def matrix_core_flops(shape, P):
+    """Matrix-core FLOPs per element (multiply-add = 2) of the affine apply on FP64 or FP32 operands:
+    tetrahedra 2 M (6 G + M), to and from the modes' gradients in the G = (P-1)P(P+1)/6 functions of
+    degree P - 2 and the mass matrix; prisms and pyramids the 7 stacked reference matrices of MK x MP
+    (K = M padded to 4, N = M padded to 16)."""
+    if shape == 2:
+        M, G = P * (P + 1) * (P + 2) // 6, (P - 1) * P * (P + 1) // 6
+        return 2 * M * (6 * G + M)
+    M = P * P * (P + 1) // 2 if shape == 1 else P * (P + 1) * (2 * P + 1) // 6
+    return 14 * ((M + 3) // 4 * 4) * ((M + 15) // 16 * 16)
+
+
 def bench_collapsed(args):
     print(json.dumps(run_collapsed(args)), flush=True)
 
@@ -425,17 +437,11 @@ def run_collapsed(args, dtypes=("f64", "f32"), generic=True):
                      "tflops": round(tfl, 2), "frac_valu": round(tfl / peak_fl, 4),
                      "frac_valu_kernel_count": round(ne * flops / ms / 1e9 / peak_fl, 4),
                      "bound": "hbm" if deformed else "alu",
-                     # the kernel that ran: batches with per-point factors take the pencil kernel
-                     # under the dense default
-                     "variant": (nir.VARIANT_PENCIL if deformed and nir.nir_get_helmholtz_variant(shape, P, dt)
-                                 == nir.VARIANT_DENSE else nir.nir_get_helmholtz_variant(shape, P, dt))}
-                if r["variant"] == nir.VARIANT_DENSE and not deformed:
-                    # the stacked GEMM on the matrix cores: 7 reference matrices of MK x MP per
-                    # element (K = M padded to 4, N = M padded to 16), 2 FLOPs per multiply-add;
-                    # dense FP64 / FP32 matrix peaks
-                    MP, MK = (M + 15) // 16 * 16, (M + 3) // 4 * 4
-                    r["tflops_mfma"] = round(ne * 14 * MK * MP / ms / 1e9, 2)
-                    r["frac_mfma"] = round(ne * 14 * MK * MP / ms / 1e9 / (78.6 if dt == nir.F64 else 157.3), 4)
+                     "variant": nir.nir_get_helmholtz_variant_of(b)}   # the kernel that ran
+                if r["variant"] == nir.VARIANT_DENSE:
+                    # against the dense FP64 / FP32 matrix peaks
+                    tflm = ne * matrix_core_flops(shape, P) / ms / 1e9
+                    r["tflops_mfma"], r["frac_mfma"] = round(tflm, 2), round(tflm / peak_fl, 4)
                 if ms_generic is not None:
                     r["generic_gdofs"] = round(ne * M / ms_generic / 1e6, 3)
                 out[f"{name}_P{P}_{dt_name}"] = r
