@@ -171,8 +171,8 @@ struct ColUnit {
 };
 
 // Planes of sweep C that stay in LDS through the point loop (P reads again at every point or point
-// pair) instead of taking 2P (FP64) or P (FP32) registers each: 0 none, 1 the third, 2 the second
-// and the third.  Per-point factors: the third in FP64 (prisms at P = 8 with two groups per CU at
+// pair) instead of taking 2P (FP64) or P (FP32) registers each: 0 none, 1 the third, 2 (affine
+// elements only) the second and the third.  Per-point factors: the third in FP64 (prisms at P = 8 with two groups per CU at
 // 128 VGPRs: 527 us with none, spilling, 312 with the third, 321 with both) and in FP32 where the
 // budget of the launch would spill otherwise (P = 6 for tetrahedra and pyramids, P >= 9); none in
 // FP32 elsewhere (tetrahedra at P = 7: 290 -> 260 us).  Affine elements, whose folded point loop
@@ -182,13 +182,6 @@ template <int SHAPE, int P, class T, bool DEF>
 constexpr int col_lds_planes() {
   if (!DEF) return sizeof(T) == 8 ? 2 : 1;
   return sizeof(T) == 8 || P >= 9 || (P == 6 && SHAPE != kPrism) ? 1 : 0;
-}
-// Whether the first point's factors are requested before sweep A and stay in flight through A and
-// B.  At P = 2 the sweeps are too short to pay for the registers (FP64 pyramids 36.4 -> 29.4 us
-// without); affine elements request point weights only.
-template <int SHAPE, int P, class T, bool DEF>
-constexpr bool col_early() {
-  return DEF && P > 2;
 }
 
 // Chain-rule factors of a point pencil (eq. (23)): d eta1 / d xi1 = 2 k1 and, with z1 = 1 + eta1,
@@ -219,8 +212,7 @@ __host__ __device__ __forceinline__ ColChain<T> col_chain(T z2, T z3) {
 // wavefronts past the last group only take part in the barriers); `lds` holds NSUB * LDS
 // values.  Every thread of the block must call it (it synchronises).
 // pen: the direction-1 factor and its derivative in [point][mode] layout (B then B').
-template <int SHAPE, int P, class T, bool DEF, int E_ = 0, int NSUB = 1, int OPM = 0, int LV = col_lds_planes<SHAPE, P, T, DEF>(),
-          bool EARLY = col_early<SHAPE, P, T, DEF>()>
+template <int SHAPE, int P, class T, bool DEF, int E_ = 0, int NSUB = 1, int OPM = 0>
 __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __restrict__ pen, const T* __restrict__ x,
                                                T* __restrict__ y, const T* __restrict__ helm, T lambda, int64_t nelmt,
                                                int64_t base0, T* __restrict__ lds0, const T* __restrict__ x1 = nullptr,
@@ -236,7 +228,9 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
   constexpr bool VTX = TET || PYR;   // a vertex mode (0,0,1) handled point by point
   using F = EoDims<P>;
   constexpr int H = F::H, NE = F::NE, NO = F::NO, ROW = F::ROW;
-  constexpr bool FOLD = !DEF, C2L = LV >= 1, C1L = LV >= 2;
+  constexpr int LV = col_lds_planes<SHAPE, P, T, DEF>();
+  constexpr bool C1L = LV == 2, C2L = LV >= 1;
+  static_assert(DEF ? !C1L : C2L, "planes in LDS of the unfolded and of the folded point loop");
 
   static_assert(E * Q <= 64, "a slice wavefront holds E elements x Q lanes");
   static_assert(!PYR || E * (2 * P - 1) <= 128, "a pyramid slice takes at most two passes of its wavefront");
@@ -282,19 +276,21 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
       const_cast<T*>(uniform_pointer(HELM && DEF ? helm + base * (7 * NQ) : tb.wq)), short(0),
       __builtin_amdgcn_readfirstlane((HELM && DEF ? ne * 7 * NQ : NQ) * int(sizeof(T))), 0x00020000);
   const int gvo = (HELM && DEF ? el * 7 * NQ + s : s) * int(sizeof(T));
-  T gn[!HELM ? 1 : (DEF ? 7 : 1) * (FOLD ? 2 : 1)];
+  T gn[!HELM ? 1 : (DEF ? 7 : 2)];
   auto request = [&](int h, bool one) {
+    if constexpr (DEF) {
 #pragma unroll
-    for (int c = 0; c < (DEF ? 7 : 1); ++c) gn[c] = buf_load<T>(grs, gvo, ((DEF ? c * NQ : 0) + h * Q2) * int(sizeof(T)));
-    if constexpr (FOLD) {
-      if (one) return;
-#pragma unroll
-      for (int c = 0; c < (DEF ? 7 : 1); ++c)
-        gn[(DEF ? 7 : 1) + c] = buf_load<T>(grs, gvo, ((DEF ? c * NQ : 0) + (Q - 1 - h) * Q2) * int(sizeof(T)));
+      for (int c = 0; c < 7; ++c) gn[c] = buf_load<T>(grs, gvo, (c * NQ + h * Q2) * int(sizeof(T)));
+    } else {
+      gn[0] = buf_load<T>(grs, gvo, h * Q2 * int(sizeof(T)));
+      if (!one) gn[1] = buf_load<T>(grs, gvo, (Q - 1 - h) * Q2 * int(sizeof(T)));
     }
   };
-  if constexpr (HELM && DEF && EARLY) {
-    if (pencils) request(0, !FOLD);
+  // at P = 2 the sweeps are too short to pay for the registers of factors in flight (FP64 pyramids
+  // 36.4 -> 29.4 us with the request after them)
+  constexpr bool EARLY = HELM && DEF && P > 2;
+  if constexpr (EARLY) {
+    if (pencils) request(0, true);
   }
 
   // ---- A: r -> k, one slice (tet: s = p+q, prism: p, pyramid: max(p,q)) per wavefront
@@ -749,7 +745,7 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
     }
     auto factors = [&](int q, T* G) {
 #pragma unroll
-      for (int c = 0; c < 7; ++c) G[c] = DEF ? gn[DEF ? 7 * q + c : 0] : ga[DEF ? 0 : c] * gn[DEF ? 0 : q];
+      for (int c = 0; c < 7; ++c) G[c] = DEF ? gn[DEF ? c : 0] : ga[DEF ? 0 : c] * gn[DEF ? 0 : q];
     };
     // a plane of this pencil that stays in LDS; the lane's offset passes an empty asm, so that the
     // addresses are formed here and not hoisted out of the loop into long-lived registers
@@ -760,8 +756,8 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
       for (int p = 0; p < P; ++p) c[p] = lds[p * Q2 + so];
     };
     T t0[P], t1[P], t2[P];
-    if constexpr (FOLD) {
-      T C0e[NE], C0o[NO], C1e[NE], C1o[NO], C2e[NE], C2o[NO];
+    if constexpr (!DEF) {
+      T C0e[NE], C0o[NO], C1e[NE], C1o[NO];
       {
         T tmp[P];
         plane(0, tmp);
@@ -770,10 +766,6 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
           plane(1, tmp);
           eo_fold<P>(tmp, C1e, C1o);
         }
-        if constexpr (!C2L) {
-          plane(2, tmp);
-          eo_fold<P>(tmp, C2e, C2o);
-        }
       }
       T E0[NE], O0[NO], E1[NE], O1[NO], E2[NE], O2[NO];
 #pragma unroll
@@ -781,7 +773,7 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
 #pragma unroll
       for (int k = 0; k < NO; ++k) O0[k] = O1[k] = O2[k] = T(0);
       if (pencils) {
-        if constexpr (!DEF || !EARLY) request(0, false);
+        request(0, false);
         // one pair (h, Q-1-h), or the middle point alone (MP): forward, pointwise, the request of
         // the next pair's factors into the registers just consumed, backward
         auto pair = [&](auto mpc, int h, bool more) {
@@ -806,13 +798,11 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
           d2[0] = S + A;
           d2[1] = S - A;
           if constexpr (C1L) __builtin_amdgcn_sched_barrier(0);   // one transient pencil at a time
-          if constexpr (C2L) {
+          {
             T tmp[P], ev[NE], od[NO];
             plane(2, tmp);
             eo_fold<P>(tmp, ev, od);
             eo_val(tk, ev, od, S, A, MP);
-          } else {
-            eo_val(tk, C2e, C2o, S, A, MP);
           }
           d3[0] = S + A;
           d3[1] = S - A;
@@ -847,14 +837,14 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
       eo_unfold<P>(E1, O1, t1);
       eo_unfold<P>(E2, O2, t2);
     } else {
-      T C0[P], C1[C1L ? 1 : P], C2[C2L ? 1 : P];
+      T C0[P], C1[P], C2[C2L ? 1 : P];
       plane(0, C0);
-      if constexpr (!C1L) plane(1, C1);
+      plane(1, C1);
       if constexpr (!C2L) plane(2, C2);
 #pragma unroll
       for (int p = 0; p < P; ++p) t0[p] = t1[p] = t2[p] = T(0);
       if (pencils) {
-        if constexpr (!DEF || !EARLY) request(0, true);
+        if constexpr (!EARLY) request(0, true);
         constexpr bool UNR = sizeof(T) == 4 || (TET ? P <= 9 : P <= 7);
 #pragma unroll(UNR ? Q : 1)
         for (int i = 0; i < Q; ++i) {
@@ -865,15 +855,8 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
             u += tk.B(i, p) * C0[p];
             d1 += tk.D(i, p) * C0[p];
           }
-          if constexpr (C1L) {
-            T c[P];
-            plane(1, c);
 #pragma unroll
-            for (int p = 0; p < P; ++p) d2 += tk.B(i, p) * c[p];
-          } else {
-#pragma unroll
-            for (int p = 0; p < P; ++p) d2 += tk.B(i, p) * C1[p];
-          }
+          for (int p = 0; p < P; ++p) d2 += tk.B(i, p) * C1[p];
           if constexpr (C2L) {
             T c[P];
             plane(2, c);
