@@ -229,7 +229,7 @@ template <int P, class T>
 constexpr GradCfg grad_cfg() {
   constexpr GradCfg c64[9] = {{4, 1, 1, 2}, {4, 1, 1, 1}, {4, 2, 1, 2}, {4, 4, 1, 2}, {4, 4, 1, 2},
                               {12, 6, 1, 1}, {8, 8, 2, 2}, {12, 12, 3, 2}, {8, 8, 1, 1}};
-  constexpr GradCfg c32[9] = {{4, 1, 1, 2}, {4, 1, 2, 1}, {4, 1, 1, 2}, {4, 4, 2, 2}, {4, 4, 1, 2},
+  constexpr GradCfg c32[9] = {{4, 1, 1, 2}, {4, 1, 1, 2}, {4, 1, 1, 2}, {4, 4, 2, 2}, {4, 4, 1, 2},
                               {6, 6, 1, 1}, {8, 8, 3, 2}, {4, 4, 3, 1}, {8, 8, 2, 1}};
   return sizeof(T) == 8 ? c64[P - 2] : c32[P - 2];
 }
