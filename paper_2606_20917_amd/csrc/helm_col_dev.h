@@ -170,6 +170,13 @@ struct ColUnit {
   T* L;
 };
 
+// Whether the point loop runs over folded point pairs (affine elements).  In FP64 at P = 2 and 3 a
+// contraction has at most two pairs and the fold saves nothing (82,944 elements at P = 2, folded -> not:
+// tetrahedra 18.1 -> 16.4 us, pyramids 18.1 -> 16.5; tetrahedra at P = 3 33.5 -> 32.2).
+template <int P, class T, bool DEF>
+constexpr bool col_fold_c() {
+  return !DEF && !(sizeof(T) == 8 && P <= 3);
+}
 // Planes of sweep C that stay in LDS through the point loop (P reads again at every point or point
 // pair) instead of taking 2P (FP64) or P (FP32) registers each: 0 none, 1 the third, 2 (affine
 // elements only) the second and the third.  Per-point factors: the third in FP64 (prisms at P = 8 with two groups per CU at
@@ -177,10 +184,10 @@ struct ColUnit {
 // budget of the launch would spill otherwise (P = 6 for tetrahedra and pyramids, P >= 9); none in
 // FP32 elsewhere (tetrahedra at P = 7: 290 -> 260 us).  Affine elements, whose folded point loop
 // needs more registers: both in FP64 (prisms at P = 8: 319, 272 and 193 us with none, the third and
-// both), the third in FP32.
+// both), the third in FP32; none where they are not folded.
 template <int SHAPE, int P, class T, bool DEF>
 constexpr int col_lds_planes() {
-  if (!DEF) return sizeof(T) == 8 ? 2 : 1;
+  if (!DEF) return sizeof(T) == 4 ? 1 : (P <= 3 ? 0 : 2);
   return sizeof(T) == 8 || P >= 9 || (P == 6 && SHAPE != kPrism) ? 1 : 0;
 }
 
@@ -230,7 +237,8 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
   constexpr int H = F::H, NE = F::NE, NO = F::NO, ROW = F::ROW;
   constexpr int LV = col_lds_planes<SHAPE, P, T, DEF>();
   constexpr bool C1L = LV == 2, C2L = LV >= 1;
-  static_assert(DEF ? !C1L : C2L, "planes in LDS of the unfolded and of the folded point loop");
+  constexpr bool FOLD = col_fold_c<P, T, DEF>();
+  static_assert(FOLD ? C2L : !C1L, "planes in LDS of the folded and of the unfolded point loop");
 
   static_assert(E * Q <= 64, "a slice wavefront holds E elements x Q lanes");
   static_assert(!PYR || E * (2 * P - 1) <= 128, "a pyramid slice takes at most two passes of its wavefront");
@@ -276,14 +284,15 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
       const_cast<T*>(uniform_pointer(HELM && DEF ? helm + base * (7 * NQ) : tb.wq)), short(0),
       __builtin_amdgcn_readfirstlane((HELM && DEF ? ne * 7 * NQ : NQ) * int(sizeof(T))), 0x00020000);
   const int gvo = (HELM && DEF ? el * 7 * NQ + s : s) * int(sizeof(T));
-  T gn[!HELM ? 1 : (DEF ? 7 : 2)];
+  T gn[!HELM ? 1 : (DEF ? 7 : (FOLD ? 2 : 1))];
   auto request = [&](int h, bool one) {
     if constexpr (DEF) {
 #pragma unroll
       for (int c = 0; c < 7; ++c) gn[c] = buf_load<T>(grs, gvo, (c * NQ + h * Q2) * int(sizeof(T)));
     } else {
       gn[0] = buf_load<T>(grs, gvo, h * Q2 * int(sizeof(T)));
-      if (!one) gn[1] = buf_load<T>(grs, gvo, (Q - 1 - h) * Q2 * int(sizeof(T)));
+      if constexpr (FOLD)
+        if (!one) gn[1] = buf_load<T>(grs, gvo, (Q - 1 - h) * Q2 * int(sizeof(T)));
     }
   };
   // at P = 2 the sweeps are too short to pay for the registers of factors in flight (FP64 pyramids
@@ -756,7 +765,7 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
       for (int p = 0; p < P; ++p) c[p] = lds[p * Q2 + so];
     };
     T t0[P], t1[P], t2[P];
-    if constexpr (!DEF) {
+    if constexpr (FOLD) {
       T C0e[NE], C0o[NO], C1e[NE], C1o[NO];
       {
         T tmp[P];
