@@ -14,14 +14,14 @@ constexpr bool eo_staged_factors() {
   return DEF && sizeof(T) == 4 && P <= 4;
 }
 
-template <int P, class T, bool DEF, int E, bool TP, bool SF = eo_staged_factors<P, T, DEF>() && !TP>
+template <int P, class T, bool DEF, int E, bool TP, bool GATHER, bool SF = eo_staged_factors<P, T, DEF>() && !TP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(hex_waves_target<P, T, E, TP>())))
 k_helm_hex_eo(const T* __restrict__ tabs, const T* __restrict__ x, T* __restrict__ y, const T* __restrict__ helm,
               const T* __restrict__ wq, T lambda, int64_t nelmt, const int32_t* __restrict__ map) {
   using D = HexPencilDims<P, T, E, TP>;
   __shared__ T lds[D::LDS + (SF ? E * 7 * D::NQ + D::BLOCK : 0)];
-  helm_hex_eo_group<P, T, DEF, E, TP, true, 1, false, SF>(tabs, x, y, helm, wq, lambda, nelmt,
-                                                           int64_t(blockIdx.x) * E, lds, nullptr, nullptr, nullptr, map);
+  helm_hex_eo_group<P, T, DEF, E, TP, true, 1, false, SF, GATHER>(
+      tabs, x, y, helm, wq, lambda, nelmt, int64_t(blockIdx.x) * E, lds, nullptr, nullptr, nullptr, map);
 }
 
 // Elements per block on per-element factors, where the sweeps and their barriers bound the kernel:
@@ -39,8 +39,11 @@ static void launch_eo_cfg(const T* tb, const T* x, T* y, const T* helm, const T*
   constexpr int E = DEF ? hex_block_elems<P, T>(TP ? kFamEOS : kFamEO) : eo_affine_elems<P>();
   using D = HexPencilDims<P, T, E, TP>;
   const int64_t nb = (nelmt + E - 1) / E;
-  hipLaunchKernelGGL((k_helm_hex_eo<P, T, DEF, E, TP>), dim3(static_cast<unsigned>(nb)), dim3(D::BLOCK), 0, s, tb,
-                     x, y, helm, wq, lam, nelmt, map);
+  const dim3 grid(static_cast<unsigned>(nb)), block(D::BLOCK);
+  if (map)   // a kernel each, as in helm_hex.hip
+    hipLaunchKernelGGL((k_helm_hex_eo<P, T, DEF, E, TP, true>), grid, block, 0, s, tb, x, y, helm, wq, lam, nelmt, map);
+  else
+    hipLaunchKernelGGL((k_helm_hex_eo<P, T, DEF, E, TP, false>), grid, block, 0, s, tb, x, y, helm, wq, lam, nelmt, map);
 }
 
 template <int P, class T>

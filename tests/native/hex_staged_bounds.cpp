@@ -29,14 +29,18 @@ static void check() {
       xg.p[x.n - 1 - k] = x.p[k];
     }
     for (size_t k = 0; k < helm.n; ++k) helm.p[k] = T(int(k * 5 % 17) - 8) / 8;
-    for (int g = 0; g < 2; ++g)
+    auto run = [&](auto gather) {
+      constexpr bool G = decltype(gather)::value;
       run_blocks(D::BLOCK, (ne + E - 1) / E,
                  [&](int64_t) { std::fill(lds.p, lds.p + lds.n, std::numeric_limits<T>::quiet_NaN()); },
                  [&](int64_t b) {
-                   helm_hex_eo_group<P, T, true, E, false, true, 1, false, true>(
-                       tabs.p, g ? xg.p : x.p, g ? yg.p : y.p, helm.p, wq.p, T(1), ne, b * E, lds.p, nullptr, nullptr,
-                       nullptr, g ? map.p : nullptr);
+                   helm_hex_eo_group<P, T, true, E, false, true, 1, false, true, G>(
+                       tabs.p, G ? xg.p : x.p, G ? yg.p : y.p, helm.p, wq.p, T(1), ne, b * E, lds.p, nullptr, nullptr,
+                       nullptr, G ? map.p : nullptr);
                  });
+    };
+    run(std::false_type{});
+    run(std::true_type{});
     for (size_t k = 0; k < y.n; ++k)
       if (!(y.p[k] == yg.p[k]) || !std::isfinite(y.p[k])) {
         std::printf("P %d, %d elements: value %zu is %g direct and %g gathered\n", P, ne, k, y.p[k], yg.p[k]);
