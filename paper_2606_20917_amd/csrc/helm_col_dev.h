@@ -296,8 +296,9 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
     }
   };
   // at P = 2 the sweeps are too short to pay for the registers of factors in flight (FP64 pyramids
-  // 36.4 -> 29.4 us with the request after them)
-  constexpr bool EARLY = HELM && DEF && P > 2;
+  // 36.4 -> 29.4 us with the request after them), nor do FP32 tetrahedra at P = 4 gain where the caches
+  // hold the factors (50,000 elements 38.9 -> 35.3 us, 65,000 48.8 -> 43.5; 82,944 67.2 -> 68.4)
+  constexpr bool EARLY = HELM && DEF && P > 2 && !(TET && P == 4 && sizeof(T) == 4);
   if constexpr (EARLY) {
     if (pencils) request(0, true);
   }
