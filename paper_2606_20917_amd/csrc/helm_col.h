@@ -61,28 +61,43 @@ constexpr ColCfg col_cfg() {
   return ColCfg{e, w};
 }
 
+// The other launch shape of FP64 tetrahedra and pyramids at P = 7: 8 elements a group, one group a CU
+// (ONE), for batches that it takes in no more rounds than pairs of groups of 7 do, to 2,048 elements and from
+// 3,585 to 4,096.  Fewer groups start, and none waits beside another.  us at 500, 900, 2,000, 2,100, 4,000
+// and 4,500 elements, pairs of 7 -> 8: tetrahedra 14.7 -> 14.4, 18.2 -> 14.8, 25.3 -> 22.0, 25.5 -> 34.5,
+// 40.0 -> 37.7, 40.7 -> 51.0; pyramids 16.2 -> 16.7, 18.8 -> 17.6, 26.3 -> 22.5, 26.7 -> 38.5, 42.8 -> 41.1,
+// 43.4 -> 56.3.
 template <int SHAPE, int P, class T, bool DEF>
-using ColKernelDims = ColDims<SHAPE, P, T, DEF ? col_cfg<SHAPE, P, T>().E : 0>;
+constexpr bool col_has_one = DEF && SHAPE != kPrism && P == 7 && sizeof(T) == 8;
+inline bool col_take_one(int64_t nelmt) {
+  constexpr int64_t CUS = 256, one = 8 * CUS, pair = 2 * 7 * CUS;
+  return (nelmt + one - 1) / one <= (nelmt + pair - 1) / pair;
+}
 
-template <int SHAPE, int P, class T, bool DEF>
-__global__ void __launch_bounds__((ColKernelDims<SHAPE, P, T, DEF>::BLOCK))
-__attribute__((amdgpu_waves_per_eu(DEF ? col_cfg<SHAPE, P, T>().W : col_waves_target<SHAPE, P, T, false>())))
+template <int SHAPE, int P, class T, bool DEF, bool ONE = false>
+using ColKernelDims = ColDims<SHAPE, P, T, DEF && !ONE ? col_cfg<SHAPE, P, T>().E : 0>;
+
+template <int SHAPE, int P, class T, bool DEF, bool ONE>
+__global__ void __launch_bounds__((ColKernelDims<SHAPE, P, T, DEF, ONE>::BLOCK))
+__attribute__((amdgpu_waves_per_eu(ONE ? 2 : (DEF ? col_cfg<SHAPE, P, T>().W : col_waves_target<SHAPE, P, T, false>()))))
     k_helm_col(DevTab<T> tb, const T* __restrict__ pen, const T* __restrict__ x, T* __restrict__ y,
                const T* __restrict__ helm, T lambda, int64_t nelmt) {
-  using D = ColKernelDims<SHAPE, P, T, DEF>;
+  using D = ColKernelDims<SHAPE, P, T, DEF, ONE>;
   extern __shared__ double dyn[];   // D::LDS values of T
   helm_col_group<SHAPE, P, T, DEF, D::E>(tb, pen, x, y, helm, lambda, nelmt, int64_t(blockIdx.x) * D::E,
                                          reinterpret_cast<T*>(dyn));
 }
 
-template <int SHAPE, int P, class T, bool DEF>
+template <int SHAPE, int P, class T, bool DEF, bool ONE = false>
 nir_status launch_col_cfg(const DevTab<T>& tb, const T* pen, const OpArgs& a, hipStream_t s) {
-  using D = ColKernelDims<SHAPE, P, T, DEF>;
+  if constexpr (col_has_one<SHAPE, P, T, DEF> && !ONE)
+    if (col_take_one(a.nelmt)) return launch_col_cfg<SHAPE, P, T, DEF, true>(tb, pen, a, s);
+  using D = ColKernelDims<SHAPE, P, T, DEF, ONE>;
   static_assert(D::LDS * sizeof(T) <= 160 * 1024, "LDS budget");
   const int64_t nb = (a.nelmt + D::E - 1) / D::E;
   if (nb > 0x7fffffff) return fail(NIR_EINVAL, "too many elements for one launch");
   if (nb == 0) return ok();
-  hipLaunchKernelGGL((k_helm_col<SHAPE, P, T, DEF>), dim3(unsigned(nb)), dim3(D::BLOCK), D::LDS * sizeof(T), s, tb, pen,
+  hipLaunchKernelGGL((k_helm_col<SHAPE, P, T, DEF, ONE>), dim3(unsigned(nb)), dim3(D::BLOCK), D::LDS * sizeof(T), s, tb, pen,
                      static_cast<const T*>(a.in0), static_cast<T*>(a.out0), static_cast<const T*>(a.helm),
                      T(a.lambda), a.nelmt);
   return hip_check(hipGetLastError(), "collapsed Helmholtz launch");

@@ -115,9 +115,9 @@ static std::vector<int64_t> counts(std::vector<int64_t> n) {
   return n;
 }
 
-template <int P, class T, bool DEF>
+template <int P, class T, bool DEF, bool ONE = false>
 static void group(const Tables<T>& t, int64_t ne, Batch<T>& b) {
-  using D = ColKernelDims<CHECK_SHAPE, P, T, DEF>;
+  using D = ColKernelDims<CHECK_SHAPE, P, T, DEF, ONE>;
   launch<T>(P, DEF ? "per-point group" : "per-element group", D::BLOCK, D::E, D::LDS, ne, b.y, [&](int64_t first, T* lds) {
     helm_col_group<CHECK_SHAPE, P, T, DEF, D::E>(t.tb, t.pen, b.x.p, b.y.p, DEF ? b.point.p : b.affine.p, T(0.75), ne, first, lds);
   });
@@ -146,6 +146,10 @@ static void order(const nir_basis* basis, const DevTab<T>& tab, const T* pen) {
     const std::vector<T> ref(b.y.p, b.y.p + b.y.n);
     group<P, T, false>(t, ne, b);
     compare(P, "per-element group", ne, b.y, ref);
+    if constexpr (col_has_one<CHECK_SHAPE, P, T, true>) {
+      group<P, T, true, true>(t, ne, b);
+      compare(P, "group of one a CU", ne, b.y, ref);
+    }
   }
   if constexpr (CHECK_SHAPE != kPyr && P <= kMixedMaxP) {
     using C = MixedCol<CHECK_SHAPE, P, T>;
