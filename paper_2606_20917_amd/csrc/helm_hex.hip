@@ -31,7 +31,7 @@
 
 namespace nir {
 
-template <int P, class T, bool DEF, int IU, int E, bool PF, bool TP, bool GP, bool GATHER>
+template <int P, class T, bool DEF, int IU, int E, bool PF, bool TP, bool GP, bool MAP>
 __global__ void __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(hex_waves_target<P, T, E, TP, (GP && DEF) ? 4 : 3>())))
 k_helm_hex(const T* __restrict__ tabs, const T* __restrict__ x,
@@ -40,7 +40,7 @@ k_helm_hex(const T* __restrict__ tabs, const T* __restrict__ x,
                                                   const int32_t* __restrict__ map) {
   // one element group per block (no grid-stride loop: the basis operands stay short-lived)
   __shared__ T lds[HexPencilDims<P, T, E, TP>::LDS];
-  helm_hex_group<P, T, DEF, IU, E, PF, TP, GP, 1, GATHER>(tabs, x, y, helm, wq, lambda, nelmt, int64_t(blockIdx.x) * E,
+  helm_hex_group<P, T, DEF, IU, E, PF, TP, GP, 1, MAP>(tabs, x, y, helm, wq, lambda, nelmt, int64_t(blockIdx.x) * E,
                                                           lds, map);
 }
 

@@ -49,10 +49,10 @@ constexpr int hex_waves_target() {
 // loop not unrolled) requests the factors of point plane i+1 when plane i is consumed, so each
 // plane's loads are in flight for a whole iteration of the point loop instead of being waited
 // for at once; plane 0 is requested after the coefficients are staged and stays in flight
-// through the forward sweeps (barriers do not wait for outstanding loads).  GATHER: the coefficients
-// are gathered, coefficient f of the batch from x[map[f]] (assembled vectors).
+// through the forward sweeps (barriers do not wait for outstanding loads).  MAP: the
+// coefficients may be gathered, coefficient f of the batch from x[map[f]] (assembled vectors; null: x[f]).
 template <int P, class T, bool DEF, int IU = 1, int E_ = 256 / ((P + 1) * (P + 1)), bool PF = false,
-          bool TP = false, bool GP = false, int NF = 1, bool GATHER = false>
+          bool TP = false, bool GP = false, int NF = 1, bool MAP = false>
 __device__ __forceinline__ void helm_hex_group(const T* __restrict__ tabs, const T* __restrict__ x, T* __restrict__ y,
                                                const T* __restrict__ helm, const T* __restrict__ wq, T lambda,
                                                int64_t nelmt, int64_t base, T* __restrict__ lds,
@@ -87,16 +87,20 @@ __device__ __forceinline__ void helm_hex_group(const T* __restrict__ tabs, const
     }
 
     // ---- stage coefficients (coalesced) into padded mode pencils
-    if constexpr (GATHER) {
-      gather_coefs<E * M, BLOCK>(x, map + base * M, ne * M, t, [&](int f, T v) {
-        const int e2 = f / M, m = f - e2 * M, pq = m / P, r = m - pq * P;
-        lds[e2 * SLAB + pq * PP + r] = v;
-      });
-    } else {
+    if constexpr (!MAP) {
       for (int f = t; f < ne * M; f += BLOCK) {
         const int e2 = f / M, m = f - e2 * M, pq = m / P, r = m - pq * P;
         lds[e2 * SLAB + pq * PP + r] = x[base * M + f];
       }
+    } else {
+      auto put = [&](int f, T v) {
+        const int e2 = f / M, m = f - e2 * M, pq = m / P, r = m - pq * P;
+        lds[e2 * SLAB + pq * PP + r] = v;
+      };
+      if (map)
+        gather_coefs<E * M, BLOCK>(x, map + base * M, ne * M, t, put);
+      else
+        for (int f = t; f < ne * M; f += BLOCK) put(f, x[base * M + f]);
     }
     __syncthreads();
 

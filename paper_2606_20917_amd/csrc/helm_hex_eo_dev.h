@@ -54,10 +54,10 @@ __device__ __forceinline__ void tri_factors(const double* J1, const double* A2, 
 // flight in registers through sweeps A and B; they are then stored into LDS after `lds`'s
 // HexPencilDims<P,T,E,TP>::LDS values, where the point loop reads them.  Every block's whole
 // factor stream is then in flight at once, as in a plain copy.  The caller's LDS holds
-// HexPencilDims<P,T,E,TP>::LDS + E 7 Q^3 + BLOCK values (the last BLOCK a junk row).  GATHER and
+// HexPencilDims<P,T,E,TP>::LDS + E 7 Q^3 + BLOCK values (the last BLOCK a junk row).  MAP and
 // map as in helm_hex_group.
 template <int P, class T, bool DEF, int E_ = 256 / ((P + 1) * (P + 1)), bool TP = false, bool GP = false,
-          int NF = 1, bool TRI = false, bool SF = false, bool GATHER = false>
+          int NF = 1, bool TRI = false, bool SF = false, bool MAP = false>
 __device__ __forceinline__ void helm_hex_eo_group(const T* __restrict__ tabs, const T* __restrict__ x,
                                                   T* __restrict__ y, const T* __restrict__ helm,
                                                   const T* __restrict__ wq, T lambda, int64_t nelmt, int64_t base,
@@ -96,7 +96,7 @@ __device__ __forceinline__ void helm_hex_eo_group(const T* __restrict__ tabs, co
     const __amdgpu_buffer_rsrc_t frs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<T*>(helm + base * NF7), short(0), (ne > 0 ? ne : 0) * NF7 * int(sizeof(T)), 0x00020000);
     T xv[PERX];
-    if constexpr (GATHER) {   // through the map; threads past the end read entry 0
+    if (MAP && map) {   // through the map; threads past the end read entry 0
       const __amdgpu_buffer_rsrc_t mrs = __builtin_amdgcn_make_buffer_rsrc(
           const_cast<int32_t*>(map + base * M), short(0), (ne > 0 ? ne : 0) * M * 4, 0x00020000);
       int32_t gi[PERX];
@@ -123,16 +123,20 @@ __device__ __forceinline__ void helm_hex_eo_group(const T* __restrict__ tabs, co
     }
   } else {
     // ---- stage coefficients (coalesced) into padded mode pencils
-    if constexpr (GATHER) {
-      gather_coefs<E * M, BLOCK>(x, map + base * M, ne * M, t, [&](int f, T v) {
-        const int e2 = f / M, m = f - e2 * M, pq = m / P, r = m - pq * P;
-        lds[e2 * SLAB + pq * PP + r] = v;
-      });
-    } else {
+    if constexpr (!MAP) {
       for (int f = t; f < ne * M; f += BLOCK) {
         const int e2 = f / M, m = f - e2 * M, pq = m / P, r = m - pq * P;
         lds[e2 * SLAB + pq * PP + r] = x[base * M + f];
       }
+    } else {
+      auto put = [&](int f, T v) {
+        const int e2 = f / M, m = f - e2 * M, pq = m / P, r = m - pq * P;
+        lds[e2 * SLAB + pq * PP + r] = v;
+      };
+      if (map)
+        gather_coefs<E * M, BLOCK>(x, map + base * M, ne * M, t, put);
+      else
+        for (int f = t; f < ne * M; f += BLOCK) put(f, x[base * M + f]);
     }
   }
   __syncthreads();
