@@ -33,10 +33,27 @@ constexpr int eo_affine_elems() {
   return P == 7 || P >= 9 ? 1 : (P == 3 ? 4 : (P == 4 ? 5 : (P == 5 ? 3 : 256 / ((P + 1) * (P + 1)))));
 }
 
-template <int P, class T, bool DEF, bool TP>
+// Counts of affine elements at which all that fit in a block (P = 5: 7 elements, P = 9 and 10: 2) run in
+// fewer rounds of the 256 CUs than the blocks above: one block of 2 a CU against two of 1 to 512, three of
+// 2 against five of 1 to 1,536 (us, blocks above -> these: FP64 at 400 elements, P = 9, 10: 10.0 -> 9.2,
+// 12.1 -> 11.3; at 1,455, P = 10: 25.8 -> 22.1, in FP32 15.1 -> 13.9; at 3,552, P = 9 in FP32 21.1 -> 19.6),
+// four of 7 against eight of 3 to 7,168 (6,938 at P = 5 in FP64 12.5 -> 11.5)
+template <int P, class T>
+constexpr bool eo_affine_wide(int64_t n) {
+  constexpr bool F64 = sizeof(T) == 8;
+  if (P == 5) return F64 && n > 6144 && n <= 7168;
+  if (P == 9) return (n > 256 && n <= 512) || (!F64 && n > 1280 && n <= 5120);
+  if (P == 10) return (F64 && n > 256 && n <= 512) || (n > 1280 && n <= 1536);
+  return false;
+}
+
+template <int P, class T, bool DEF, bool TP, bool WIDE = false>
 static void launch_eo_cfg(const T* tb, const T* x, T* y, const T* helm, const T* wq, T lam, int64_t nelmt,
                           const int32_t* map, hipStream_t s) {
-  constexpr int E = DEF ? hex_block_elems<P, T>(TP ? kFamEOS : kFamEO) : eo_affine_elems<P>();
+  if constexpr (!DEF && !TP && !WIDE && ((P == 5 && sizeof(T) == 8) || P >= 9))
+    if (eo_affine_wide<P, T>(nelmt)) return launch_eo_cfg<P, T, DEF, TP, true>(tb, x, y, helm, wq, lam, nelmt, map, s);
+  constexpr int E = DEF    ? hex_block_elems<P, T>(TP ? kFamEOS : kFamEO)
+                    : WIDE ? 256 / ((P + 1) * (P + 1)) : eo_affine_elems<P>();
   using D = HexPencilDims<P, T, E, TP>;
   const int64_t nb = (nelmt + E - 1) / E;
   const dim3 grid(static_cast<unsigned>(nb)), block(D::BLOCK);
