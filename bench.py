@@ -138,7 +138,7 @@ def cpu_baseline(cases, budget_s):
 # HBM bytes per launch of the dominant kernel measured with FETCH_SIZE / WRITE_SIZE (calibrated
 # by a plain 1 GiB copy: FETCH_SIZE x 2.0, WRITE_SIZE x 1.0), valid for that kernel variant while
 # the kernel sources hash to `src_sha`
-TRAFFIC = {"P": 10, "dtype": "f64", "variant": 9, "bytes": 2973911839, "src_sha": "30bbd60a4ac71b93"}
+TRAFFIC = {"P": 10, "dtype": "f64", "variant": 9, "bytes": 2973592993, "src_sha": "a5b3b1b805de37b1"}
 
 
 def kernel_src_sha():
