@@ -38,10 +38,10 @@
 // unfolded: a pair of points holds twice the factors and values, about 30 FP64 registers more, and
 // the spills cost more than the arithmetic saved (tetrahedra at P = 6 in FP64 420 -> 663 us); where
 // it fits with two planes in LDS, the pairs' longer chain does (pyramids at P = 5 283 -> 312 us, prisms
-// at P = 8 287 -> 362).  What bounds it there is the factor stream against the sweeps that stream nothing, hence the first
-// point's factors in flight through A and B and buffer loads without address arithmetic.  24^3
-// cubes, FP64, before and after: prisms at P = 8 370 -> 287 us (3.4 -> 4.4 TB/s), at P = 10 824 ->
-// 638; pyramids at P = 5 321 -> 282, at P = 7 866 -> 586; tetrahedra at P = 7 749 -> 548 us.
+// at P = 8 287 -> 362).  What bounds it there is the factor stream against the sweeps that stream
+// nothing, hence the first point's factors in flight through A and B and buffer loads without address
+// arithmetic.  24^3 cubes, FP64, before and after: prisms at P = 8 370 -> 287 us (3.4 -> 4.4 TB/s), at P
+// = 10 824 -> 638; pyramids at P = 5 321 -> 282, at P = 7 768 -> 617; tetrahedra at P = 7 697 -> 582 us.
 //
 // LDS per element (values of T): one region of 3 P Q^2 values that holds, in turn, the
 // coefficients, the A rows, the B planes, the C^T planes, the B^T rows and the results;
@@ -179,10 +179,10 @@ constexpr bool col_fold_c() {
 }
 // Planes of sweep C that stay in LDS through the point loop (P reads again at every point or point
 // pair) instead of taking 2P (FP64) or P (FP32) registers each: 0 none, 1 the third, 2 (affine
-// elements only) the second and the third.  Per-point factors: the third in FP64 (prisms at P = 8 with two groups per CU at
-// 128 VGPRs: 527 us with none, spilling, 312 with the third, 321 with both) and in FP32 where the
-// budget of the launch would spill otherwise (P = 6 for tetrahedra and pyramids, P >= 9); none in
-// FP32 elsewhere (tetrahedra at P = 7: 290 -> 260 us).  Affine elements, whose folded point loop
+// elements only) the second and the third.  Per-point factors: the third in FP64 (prisms at P = 8 with
+// two groups per CU at 128 VGPRs: 527 us with none, spilling, 312 with the third, 321 with both) and in
+// FP32 where the budget of the launch would spill otherwise (P = 6 for tetrahedra and pyramids, P >= 9);
+// none in FP32 elsewhere (tetrahedra at P = 7: 290 -> 260 us).  Affine elements, whose folded point loop
 // needs more registers: both in FP64 (prisms at P = 8: 319, 272 and 193 us with none, the third and
 // both), the third in FP32; none where they are not folded.
 template <int SHAPE, int P, class T, bool DEF>
@@ -497,7 +497,7 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
           static_assert(nt == nq + (X ? 1 : 0), "B terms");
           constexpr int RB = col_row_batch<SHAPE, P, T>((BWD ? 1 : 2) * nt);
           const_ptr<T> f0 = nullptr, df0 = nullptr;
-  #pragma unroll
+#pragma unroll
           for (int j = 0; j < Q; ++j) {
             if (j % RB == 0) {
               const T dep = j > 0 ? b0[j - 1] : av[0];
@@ -506,7 +506,7 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
             }
             const const_ptr<T> f = f0 + j * nt, df = df0 + j * nt;
             T v0 = T(0), v1 = T(0), v2 = T(0);
-  #pragma unroll
+#pragma unroll
             for (int q = 0; q < nt; ++q) {
               v0 += f[q] * av[q];
               if constexpr (!BWD) {
@@ -937,11 +937,11 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
           // row is live in SGPRs; the pair (0,1) term last for X
           constexpr int nt = col_b_terms(SHAPE, P, pc);
           constexpr int off = col_b_off(SHAPE, P, pc);
-  #pragma unroll
+#pragma unroll
           for (int q = 0; q < nt; ++q) s0[q] = s1[q] = T(0);
           constexpr int RB = col_row_batch<SHAPE, P, T>((IPR ? 1 : 2) * nt);
           const_ptr<T> f0 = nullptr, df0 = nullptr;
-  #pragma unroll
+#pragma unroll
           for (int j = 0; j < Q; ++j) {
             if (j % RB == 0) {
               const T dep = j > 0 ? (IPR ? s0[nt - 1] : s1[nt - 1]) : tv0[0];
@@ -949,7 +949,7 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
               df0 = fresh_table_after(tb.dT2t, dep) + off;
             }
             const const_ptr<T> f = f0 + j * nt, df = df0 + j * nt;
-  #pragma unroll
+#pragma unroll
             for (int q = 0; q < nt; ++q) {
               s0[q] += f[q] * tv0[j];
               if constexpr (!IPR) {
