@@ -137,6 +137,14 @@ struct ColDims {
   static constexpr int LDS = E * SLAB;
 };
 
+constexpr int kMixedBlock = 512;   // threads per workgroup of the persistent mixed kernel
+// elements of a group in that kernel: full slice wavefronts, at most its threads and 64 KiB of LDS
+template <int SHAPE, int P, class T>
+constexpr int col_mixed_elems() {
+  constexpr int Q = P + 1, e = (64 / Q) < (kMixedBlock / (Q * Q)) ? (64 / Q) : (kMixedBlock / (Q * Q));
+  return e < ColDims<SHAPE, P, T>::EL64 ? e : ColDims<SHAPE, P, T>::EL64;
+}
+
 // calls f(integral_constant<I>) for the I == v (v uniform across the wavefront)
 template <int I, int N, class F>
 __device__ __forceinline__ void col_dispatch(int v, F& f) {
@@ -241,6 +249,9 @@ __device__ __forceinline__ void helm_col_group(const DevTab<T>& tb, const T* __r
   static_assert(FOLD ? C2L : !C1L, "planes in LDS of the folded and of the unfolded point loop");
 
   static_assert(E * Q <= 64, "a slice wavefront holds E elements x Q lanes");
+  // affine Helmholtz groups come in these two shapes only: others faulted in a sweep, of unknown cause
+  static_assert(OPM != 0 || DEF || E == ColDims<SHAPE, P, T>::E || E == col_mixed_elems<SHAPE, P, T>(),
+                "affine group size");
   static_assert(!PYR || E * (2 * P - 1) <= 128, "a pyramid slice takes at most two passes of its wavefront");
   const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int sub = wave0 / D::NW;                       // group of this wavefront

@@ -12,7 +12,6 @@
 namespace nir {
 
 constexpr int kMixedMaxP = 8;      // orders compiled into the persistent kernel
-constexpr int kMixedBlock = 512;   // threads per workgroup of the persistent kernel
 
 template <class T>
 struct MixedBatch {
@@ -47,8 +46,7 @@ struct MixedHex {
 template <int S, int P, class T>
 struct MixedCol {
   static constexpr int Q = P + 1;
-  static constexpr int E0 = (64 / Q) < (kMixedBlock / (Q * Q)) ? (64 / Q) : (kMixedBlock / (Q * Q));
-  static constexpr int E = E0 < ColDims<S, P, T>::EL64 ? E0 : ColDims<S, P, T>::EL64;
+  static constexpr int E = col_mixed_elems<S, P, T>();
   using D = ColDims<S, P, T, E>;
   static constexpr int NS0 = kMixedBlock / D::BLOCK;
   static constexpr int NSL = (65536 / int(sizeof(T))) / D::LDS;
