@@ -34,6 +34,15 @@ def _run(tmp_path, name, sanitize=SANITIZERS, sources=(), flags=("-O1", "-g")):
     assert " 0 failures" in r.stdout
 
 
+def _thread_sanitizer_runs(tmp_path):
+    """Whether a program under ThreadSanitizer starts here (it needs a memory layout that some kernels'
+    address randomisation does not give)."""
+    src, exe = tmp_path / "probe.cpp", str(tmp_path / "probe")
+    src.write_text("int main() { return 0; }\n")
+    built = subprocess.run(["g++", "-fsanitize=thread", str(src), "-o", exe], capture_output=True, timeout=120)
+    return built.returncode == 0 and subprocess.run([exe], capture_output=True, timeout=60).returncode == 0
+
+
 def test_half_conversion_rounds_to_nearest_even(tmp_path):
     _run(tmp_path, "half_bits", flags=("-O2",))
 
@@ -44,7 +53,7 @@ def test_staged_hexahedral_groups_stay_in_bounds(tmp_path):
 
 @pytest.mark.parametrize("shape", [1, 2, 3], ids=["prism", "tet", "pyr"])
 def test_collapsed_groups_stay_in_bounds(shape, tmp_path):
-    """Every order under AddressSanitizer, two of them under ThreadSanitizer."""
+    """Every order under AddressSanitizer, two of them under ThreadSanitizer where it runs."""
     sources = [os.path.join(CSRC, f) for f in ("api.cpp", "tables.cpp")]
 
     def one(job):
@@ -54,7 +63,8 @@ def test_collapsed_groups_stay_in_bounds(shape, tmp_path):
                  f"-DCHECK_PMIN={P}", f"-DCHECK_PMAX={P}")
         _run(tmp_path, "col_bounds", sanitize, sources, flags)
 
-    jobs = [(P, "address") for P in range(10, 1, -1)] + [(P, "thread") for P in (6, 3)]
+    threads = _thread_sanitizer_runs(tmp_path)
+    jobs = [(P, "address") for P in range(10, 1, -1)] + [(P, "thread") for P in (6, 3) if threads]
     with cf.ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as ex:
         list(ex.map(one, jobs))
 
